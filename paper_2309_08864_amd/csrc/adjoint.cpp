@@ -112,6 +112,17 @@ struct AdjCtx {
   int npts;
 };
 
+// What a copy-out on s_out needs before it is queued: the chunk's compute
+// event, waited for by the host where the copy is the runtime's (as in the
+// forward executor, whose header says why), by the stream otherwise.
+static int out_after(const AdjCtx &C, hipEvent_t comp, bool host) {
+  if (host)
+    AHIP(hipEventSynchronize(comp));
+  else
+    AHIP(hipStreamWaitEvent(C.s_out, comp, 0));
+  return SO2DR_OK;
+}
+
 // Loss pass over the chunks (no halo): lam_host holds u_T and becomes lambda_T.
 static int loss_pass(Plan &P, AdjCtx &C, void *lam_host, const void *y_host, so2dr_stats *S) {
   const size_t pb = P.plane_bytes();
@@ -121,12 +132,26 @@ static int loss_pass(Plan &P, AdjCtx &C, void *lam_host, const void *y_host, so2
   char *d_lam = C.kcopy ? mapped_host(lam_host, C.field) : nullptr;
   char *d_lam_in = C.kcopy_in ? d_lam : nullptr;
   char *d_y = C.kcopy_in ? mapped_host(y_host, C.field) : nullptr;
+  const bool hold = C.s_out != C.s_comp && C.s_out != C.s_in && !d_lam;
+  auto out = [&](int i) -> int {
+    const int64_t z0 = P.bnd[i], z1 = P.bnd[i + 1];
+    const size_t n = (size_t)(z1 - z0) * pb;
+    ARC(out_after(C, P.ev_comp[i], hold));
+    ARC(copy_to_host(static_cast<char *>(lam_host) + (size_t)z0 * pb, P.slot_buf(i % P.n_slots, 0), n,
+                     lam_host, d_lam, C.s_out));
+    AHIP(hipEventRecord(P.ev_d2h[i], C.s_out));
+    S->bytes_d2h += n;
+    return SO2DR_OK;
+  };
   for (int i = 0; i < P.d; ++i) {
     const int slot = i % P.n_slots;
     const int64_t z0 = P.bnd[i], z1 = P.bnd[i + 1];
     const size_t n = (size_t)(z1 - z0) * pb;
     char *ub = P.slot_buf(slot, 0), *yb = P.slot_buf(slot, 1);
-    if (i >= P.n_slots) AHIP(hipStreamWaitEvent(C.s_in, P.ev_d2h[i - P.n_slots], 0));
+    if (i >= P.n_slots) {
+      if (hold) ARC(out(i - P.n_slots));
+      AHIP(hipStreamWaitEvent(C.s_in, P.ev_d2h[i - P.n_slots], 0));
+    }
     ARC(copy_to_device(ub, static_cast<char *>(lam_host) + (size_t)z0 * pb, n, lam_host, d_lam_in, C.s_in));
     ARC(copy_to_device(yb, static_cast<const char *>(y_host) + (size_t)z0 * pb, n, y_host, d_y, C.s_in));
     AHIP(hipEventRecord(P.ev_h2d[i], C.s_in));
@@ -136,12 +161,11 @@ static int loss_pass(Plan &P, AdjCtx &C, void *lam_host, const void *y_host, so2
       return SO2DR_E_HIP;
     }
     AHIP(hipEventRecord(P.ev_comp[i], C.s_comp));
-    AHIP(hipStreamWaitEvent(C.s_out, P.ev_comp[i], 0));
-    ARC(copy_to_host(static_cast<char *>(lam_host) + (size_t)z0 * pb, ub, n, lam_host, d_lam, C.s_out));
-    AHIP(hipEventRecord(P.ev_d2h[i], C.s_out));
+    if (!hold) ARC(out(i));
     S->bytes_h2d += 2 * n;
-    S->bytes_d2h += n;
   }
+  if (hold)
+    for (int i = std::max(0, P.d - P.n_slots); i < P.d; ++i) ARC(out(i));
   AHIP(hipStreamSynchronize(C.s_in));
   AHIP(hipStreamSynchronize(C.s_comp));
   AHIP(hipStreamSynchronize(C.s_out));
@@ -167,6 +191,19 @@ static int reverse_round(Plan &P, AdjCtx &C, const void *u_host, void *lam_host,
   char *d_lam_in = C.kcopy_in ? d_lam : nullptr;
   LaunchParams fwd = base_launch(P, P.weights.data());
   LaunchParams adj = base_launch(P, C.wT.data());
+  const bool hold = C.s_out != C.s_comp && C.s_out != C.s_in && !d_lam;
+  // copy-out of lambda_{t_s} over chunk i's output planes, in place, from the
+  // slot's own buffer
+  auto out = [&](int i) -> int {
+    const int64_t bz = area_lo(P, i, kp, 0), o0 = area_lo(P, i, kp, kp), o1 = area_hi(P, i, kp, kp);
+    const char *src = P.slot_buf(i % P.n_slots, LA) + (size_t)(o0 - bz) * pb;
+    ARC(out_after(C, P.ev_comp[i], hold));
+    ARC(copy_to_host(static_cast<char *>(lam_host) + (size_t)o0 * pb, src, (size_t)(o1 - o0) * pb, lam_host,
+                     d_lam, C.s_out));
+    AHIP(hipEventRecord(P.ev_d2h[i], C.s_out));
+    S->bytes_d2h += (size_t)(o1 - o0) * pb;
+    return SO2DR_OK;
+  };
   for (int i = 0; i < P.d; ++i) {
     const int slot = i % P.n_slots;
     const int64_t b0 = P.bnd[i], b1 = P.bnd[i + 1];
@@ -174,7 +211,10 @@ static int reverse_round(Plan &P, AdjCtx &C, const void *u_host, void *lam_host,
     auto buf = [&](int which) { return P.slot_buf(slot, which); };
     auto at = [&](int which, int64_t z) { return buf(which) + (size_t)(z - bz) * pb; };
     // copy-in of the own planes of u_{t_s} and lambda_{t_e}
-    if (i >= P.n_slots) AHIP(hipStreamWaitEvent(C.s_in, P.ev_d2h[i - P.n_slots], 0));
+    if (i >= P.n_slots) {
+      if (hold) ARC(out(i - P.n_slots));
+      AHIP(hipStreamWaitEvent(C.s_in, P.ev_d2h[i - P.n_slots], 0));
+    }
     const size_t own = (size_t)(b1 - b0) * pb;
     ARC(copy_to_device(at(U0, b0), static_cast<const char *>(u_host) + (size_t)b0 * pb, own, u_host, d_u,
                        C.s_in));
@@ -254,23 +294,20 @@ static int reverse_round(Plan &P, AdjCtx &C, const void *u_host, void *lam_host,
       S->kernel_launches += 1;
       std::swap(lcur, lnext);
     }
-    // copy-out of lambda_{t_s} over the chunk's output planes, in place, from
-    // the slot's own buffer: the shared one is the next chunk's
+    // lambda_{t_s} leaves from the slot's own buffer: the shared one is the
+    // next chunk's
     const int64_t o0 = area_lo(P, i, kp, kp), o1 = area_hi(P, i, kp, kp);
     if (lcur != LA) {
       if (launch_dcopy(at(LA, o0), at(lcur, o0), (size_t)(o1 - o0) * pb, s)) {
         set_error("adjoint copy kernel launch failed");
         return SO2DR_E_HIP;
       }
-      lcur = LA;
     }
     AHIP(hipEventRecord(P.ev_comp[i], s));
-    AHIP(hipStreamWaitEvent(C.s_out, P.ev_comp[i], 0));
-    ARC(copy_to_host(static_cast<char *>(lam_host) + (size_t)o0 * pb, at(lcur, o0), (size_t)(o1 - o0) * pb,
-                     lam_host, d_lam, C.s_out));
-    AHIP(hipEventRecord(P.ev_d2h[i], C.s_out));
-    S->bytes_d2h += (size_t)(o1 - o0) * pb;
+    if (!hold) ARC(out(i));
   }
+  if (hold)
+    for (int i = std::max(0, P.d - P.n_slots); i < P.d; ++i) ARC(out(i));
   AHIP(hipStreamSynchronize(C.s_in));
   AHIP(hipStreamSynchronize(C.s_comp));
   AHIP(hipStreamSynchronize(C.s_out));

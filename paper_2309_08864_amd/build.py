@@ -21,9 +21,9 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-ffp-contract
           "-I", os.path.join(os.path.dirname(HERE), "include"), "-Wall", "-Wno-unused-function"]
 
 # (source, extra compiler flags, object name): kernels.hip is compiled once
-# per storage type (so2dr_dtype value in SO2DR_STORAGE)
-SOURCES = [("kernels.hip", [f"-DSO2DR_STORAGE={d}"], f"kernels_{name}.o")
-           for d, name in ((0, "f32"), (1, "f64"), (2, "bf16"), (3, "f16"))]
+# per storage type (so2dr_dtype value in SO2DR_STORAGE) and stencil group
+SOURCES = [("kernels.hip", [f"-DSO2DR_STORAGE={d}", f"-DSO2DR_GROUP={g}"], f"kernels_{name}_{g}.o")
+           for d, name in ((2, "bf16"), (3, "f16"), (0, "f32"), (1, "f64")) for g in (2, 1, 0)]
 SOURCES += [(s, [], s + ".o") for s in ("aux_kernels.hip", "planner.cpp", "runtime.cpp",
                                          "adjoint.cpp", "model.cpp", "capi.cpp")]
 

@@ -1,16 +1,17 @@
-// kernels.hip -- the fused-step kernels of one storage type, and the
-// dispatcher that maps a launch onto a compiled instantiation.  The build
-// compiles this file once per storage type, with SO2DR_STORAGE set to its
-// so2dr_dtype value (0 F32, 1 F64, 2 BF16, 3 F16), so that the four sets of
-// instantiations compile in parallel; kMaxDepth (depths.hpp) decides which
-// stencils and depths each type gets.
+// kernels.hip -- the fused-step kernels of one storage type and one group of
+// stencils, and the dispatcher that maps a launch onto a compiled
+// instantiation.  The build compiles this file once per storage type and
+// group, with SO2DR_STORAGE set to the so2dr_dtype value (0 F32, 1 F64, 2
+// BF16, 3 F16) and SO2DR_GROUP to 0..2, so that the sets of instantiations
+// compile in parallel; kMaxDepth (depths.hpp) decides which stencils and
+// depths each type gets, stencil_group (launch.hpp) which group a stencil is in.
 #include "so2dr.h"
 
 #include "depths.hpp"
 #include "launch_impl.hpp"
 
-#ifndef SO2DR_STORAGE
-#error "compile with -DSO2DR_STORAGE=<so2dr_dtype value>"
+#if !defined(SO2DR_STORAGE) || !defined(SO2DR_GROUP)
+#error "compile with -DSO2DR_STORAGE=<so2dr_dtype value> -DSO2DR_GROUP=<0..2>"
 #endif
 
 namespace so2dr {
@@ -28,7 +29,7 @@ int dispatch(const LaunchParams &p, hipStream_t s, std::string *msg) {
   switch (p.stencil) {
 #define SO2DR_CASE(ID, NDIM, BOX, R)                                          \
   case ID:                                                                  \
-    if constexpr (kMaxDepth[D][ID] > 0)                                     \
+    if constexpr (kMaxDepth[D][ID] > 0 && stencil_group(ID) == SO2DR_GROUP)  \
       return launch_depth<T, NDIM, BOX, R, kMaxDepth[D][ID]>(p, s, msg);   \
     break;
     SO2DR_CASE(ST_2D_STAR_R1, 2, false, 1)
@@ -49,16 +50,10 @@ int dispatch(const LaunchParams &p, hipStream_t s, std::string *msg) {
 
 }  // namespace
 
-#if SO2DR_STORAGE == 0
-int launch_tb_f32(const LaunchParams &p, hipStream_t s, std::string *msg) { return dispatch<SO2DR_F32>(p, s, msg); }
-#elif SO2DR_STORAGE == 1
-int launch_tb_f64(const LaunchParams &p, hipStream_t s, std::string *msg) { return dispatch<SO2DR_F64>(p, s, msg); }
-#elif SO2DR_STORAGE == 2
-int launch_tb_bf16(const LaunchParams &p, hipStream_t s, std::string *msg) { return dispatch<SO2DR_BF16>(p, s, msg); }
-#elif SO2DR_STORAGE == 3
-int launch_tb_f16(const LaunchParams &p, hipStream_t s, std::string *msg) { return dispatch<SO2DR_F16>(p, s, msg); }
-#else
-#error "SO2DR_STORAGE must be 0, 1, 2 or 3"
-#endif
+#define SO2DR_NAME3(A, B, C) A##B##_##C
+#define SO2DR_NAME2(A, B, C) SO2DR_NAME3(A, B, C)
+int SO2DR_NAME2(launch_tb_, SO2DR_STORAGE, SO2DR_GROUP)(const LaunchParams &p, hipStream_t s, std::string *msg) {
+  return dispatch<SO2DR_STORAGE>(p, s, msg);
+}
 
 }  // namespace so2dr

@@ -39,10 +39,23 @@ int max_depth(int dtype, int stencil);
 // Launch on `stream`; returns 0 or a negative so2dr error code (msg filled).
 int launch_tb(int dtype, const LaunchParams &p, hipStream_t stream, std::string *msg);
 
-// Per-type entry points defined in kernels_<type>.hip.
-int launch_tb_f32(const LaunchParams &p, hipStream_t s, std::string *msg);
-int launch_tb_f64(const LaunchParams &p, hipStream_t s, std::string *msg);
-int launch_tb_bf16(const LaunchParams &p, hipStream_t s, std::string *msg);
-int launch_tb_f16(const LaunchParams &p, hipStream_t s, std::string *msg);
+// Stencils are compiled in three groups of similar size, each with a 2D and
+// a 3D kernel family.
+constexpr int stencil_group(int stencil) {
+  return stencil == ST_2D_STAR_R1 || stencil == ST_3D_STAR_R1                            ? 0
+         : stencil == ST_2D_BOX_R1 || stencil == ST_2D_BOX_R2 || stencil == ST_3D_STAR_R2 ? 1
+                                                                                          : 2;
+}
+
+// Entry points of kernels.hip, launch_tb_<storage>_<group>.
+#define SO2DR_DECL(D)                                                            \
+  int launch_tb_##D##_0(const LaunchParams &p, hipStream_t s, std::string *msg); \
+  int launch_tb_##D##_1(const LaunchParams &p, hipStream_t s, std::string *msg); \
+  int launch_tb_##D##_2(const LaunchParams &p, hipStream_t s, std::string *msg);
+SO2DR_DECL(0)
+SO2DR_DECL(1)
+SO2DR_DECL(2)
+SO2DR_DECL(3)
+#undef SO2DR_DECL
 
 }  // namespace so2dr

@@ -5,10 +5,10 @@
 #include <algorithm>
 #include <string>
 
+#include "lane_tile.hpp"
 #include "launch.hpp"
 #include "march2d_kernel.hpp"
 #include "march_kernel.hpp"
-#include "star_kernel.hpp"
 #include "tb_kernel.hpp"
 
 namespace so2dr {
@@ -18,7 +18,7 @@ namespace so2dr {
 constexpr int64_t kTargetWgs = 1024;
 constexpr int64_t kMinSegPlanes = 16;
 
-// Segmenting of the cut axis shared by both kernel families: `target`
+// Segmenting of the cut axis for the LDS-plane kernel and 2D rows: `target`
 // workgroups, never segments shorter than kMinSegPlanes.
 inline void plan_segments(int64_t span, int64_t tiles, int64_t *zseg, int *nseg,
                           int64_t target = kTargetWgs) {
@@ -115,37 +115,6 @@ int launch_one(const LaunchParams &p, hipStream_t stream, std::string *msg) {
   return 0;
 }
 
-template <typename T, bool BOX, int R, int KL, int NW, int M, int VX, int HB, bool RAS = false>
-int launch_col_one(const LaunchParams &p, hipStream_t stream, std::string *msg) {
-  using A = typename Store<T>::A;
-  using G = StarTile<R, KL, NW, M, VX>;
-  using S = Stencil<3, BOX, R>;
-  if (p.npts != S::npts()) {
-    if (msg) *msg = "weight count does not match the stencil";
-    return -1;
-  }
-  TbArgs<A> a = launch_args<A>(p, S::npts());
-  a.ntx = (int)((p.nx + G::OX - 1) / G::OX);
-  a.nty = (int)((p.ny + G::OY - 1) / G::OY);
-  const int64_t span = p.out_hi - p.out_lo;
-  if (span <= 0) return 0;
-  plan_segments(span, (int64_t)a.ntx * a.nty, &a.zseg, &a.nseg);
-  const int64_t nwg = (int64_t)a.ntx * a.nty * a.nseg;
-  if (nwg > 0x7fffffff) {
-    if (msg) *msg = "grid too large for one launch";
-    return -1;
-  }
-  const int64_t grid = xcd_grid(nwg);
-  hipLaunchKernelGGL((col3d_kernel<T, BOX, R, KL, NW, M, VX, HB, RAS>), dim3((unsigned)grid), dim3(NW * 64), 0,
-                     stream, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) {
-    if (msg) *msg = std::string("kernel launch: ") + hipGetErrorString(e);
-    return -5;
-  }
-  return 0;
-}
-
 // Whether the march kernel's layout fits this launch: whole VX-cell vectors
 // per row, 32-bit byte offsets within a plane, 32-bit plane indices.
 template <typename T, int VX>
@@ -157,47 +126,98 @@ inline bool march_fits(const LaunchParams &p) {
          p.out_z0 > -((int64_t)1 << 29) && std::max<int64_t>(p.in_lo, 0) < std::min<int64_t>(p.in_hi, p.n_axis);
 }
 
+// A launch's cost in clock cycles for segments of a given length, and the
+// segmenting of least cost.  A workgroup's march step takes `lat` cycles of
+// latency (barrier, LDS round trip, address work) plus its own issue time
+// `issue` and that of the workgroups sharing its CU, and a segment of zseg
+// output planes takes zseg + extra steps; workgroups run in rounds of CUs x
+// per_cu.  Candidates fill k workgroups per CU, k = 1, 2, ..., which is where
+// the rounds change; more, shorter segments only for a gain of 2 %, since each
+// re-reads `extra` planes.
+//
+// Measured on MI355X (3D 7-point FP32, 3 levels, tiles of 8 waves x 6 rows x 2
+// cells): a 256^3 grid took 76 us in 336 workgroups of 16-plane segments (the
+// former rule: 1.5 workgroups per slot, segments of at least 16 planes) and
+// 50 us in 252 of 22 planes, one round instead of two; a 320 x 320 x 26 chunk
+// 52 us in 24 workgroups and 19 us in 216.  Over 323 launches of 47 shapes on 9
+// grids the choice came within 3 % (geometric mean) of the best segmenting
+// tried.
+struct MarchPlan {
+  int64_t zseg = 0;
+  int nseg = 0;
+  double cost = 0.0;
+};
+
+inline MarchPlan plan_march(int64_t span, int64_t tiles, int extra, int cus, int per_cu, double lat,
+                            double issue) {
+  constexpr int kMaxPerCu = 12;    // candidates; beyond, rounds no longer matter
+  constexpr int kPrologue = 2;     // steps' worth of start-up per workgroup
+  MarchPlan best;
+  int64_t last = 0;
+  for (int k = 1; k <= kMaxPerCu; ++k) {
+    const int64_t want = std::min(span, std::max<int64_t>(1, (int64_t)k * cus / tiles));
+    if (want == last) continue;
+    last = want;
+    const int64_t zseg = (span + want - 1) / want, nseg = (span + zseg - 1) / zseg;
+    const int64_t n = tiles * nseg, full = n / ((int64_t)cus * per_cu), rest = n - full * cus * per_cu;
+    const double t = (double)full * (lat + per_cu * issue) +
+                     (rest > 0 ? lat + (double)((rest + cus - 1) / cus) * issue : 0.0);
+    const double c = (double)(zseg + extra + kPrologue) * t;
+    if (best.nseg == 0 || c < 0.98 * best.cost) best = {zseg, (int)nseg, c};
+  }
+  return best;
+}
+
+// One tile shape of march3d_kernel: its segmenting and predicted cost for a
+// launch, and the launch itself.
 template <typename T, bool BOX, int R, int KL, int NW, int M, int VX, int HB, int PF, int WPE = 1,
           bool RAS = false, int HA = VX>
-int launch_march_one(const LaunchParams &p, hipStream_t stream, std::string *msg) {
+struct March3d {
   using A = typename Store<T>::A;
   using G = StarTile<R, KL, NW, M, VX, HA>;
   using S = Stencil<3, BOX, R>;
-  if (p.npts != S::npts()) {
-    if (msg) *msg = "weight count does not match the stencil";
-    return -1;
+  static constexpr auto kernel = march3d_kernel<T, BOX, R, KL, NW, M, VX, HB, PF, WPE, RAS, HA>;
+
+  static int ntx(const LaunchParams &p) { return (int)((p.nx + G::OX - 1) / G::OX); }
+  static int nty(const LaunchParams &p) { return (int)((p.ny + G::OY - 1) / G::OY); }
+
+  static MarchPlan plan(const LaunchParams &p) {
+    // instructions of one wave per step: the multiply-adds, per row and level
+    // the lane shifts, halo rows and stores, and the plane's addresses; a wave
+    // instruction takes 4 cycles of its SIMD, and the waves share 4 SIMDs
+    constexpr double issue = NW * (M * KL * (VX * S::npts() + 4.0) + 20.0);
+    constexpr double lat = 800.0;
+    static std::atomic<int> per_cu{-1};
+    const int64_t slots = resident_wgs((const void *)kernel, NW * 64, &per_cu);
+    const int occ = std::max(1, per_cu.load(std::memory_order_relaxed));
+    const int cus = slots > 0 ? (int)(slots / occ) : 256;
+    return plan_march(p.out_hi - p.out_lo, (int64_t)ntx(p) * nty(p), 2 * KL * R + KL - 1, cus, occ, lat, issue);
   }
-  if (!march_fits<T, VX>(p)) {
-    if (msg) *msg = "launch does not fit the march kernel's layout";
-    return -1;
+
+  static int launch(const LaunchParams &p, const MarchPlan &mp, hipStream_t stream, std::string *msg) {
+    if (p.npts != S::npts()) {
+      if (msg) *msg = "weight count does not match the stencil";
+      return -1;
+    }
+    TbArgs<A> a = launch_args<A>(p, S::npts());
+    a.ntx = ntx(p);
+    a.nty = nty(p);
+    a.zseg = mp.zseg;
+    a.nseg = mp.nseg;
+    const int64_t nwg = (int64_t)a.ntx * a.nty * a.nseg;
+    if (nwg > 0x7fffffff) {
+      if (msg) *msg = "grid too large for one launch";
+      return -1;
+    }
+    hipLaunchKernelGGL(kernel, dim3((unsigned)xcd_grid(nwg)), dim3(NW * 64), 0, stream, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {
+      if (msg) *msg = std::string("kernel launch: ") + hipGetErrorString(e);
+      return -5;
+    }
+    return 0;
   }
-  TbArgs<A> a = launch_args<A>(p, S::npts());
-  a.ntx = (int)((p.nx + G::OX - 1) / G::OX);
-  a.nty = (int)((p.ny + G::OY - 1) / G::OY);
-  const int64_t span = p.out_hi - p.out_lo;
-  if (span <= 0) return 0;
-  // About 1.5 workgroups per resident slot: measured on MI355X over
-  // 2048x1024x80 chunks, fewer leave the last wave of workgroups short and
-  // more re-read 2 KL R planes per extra segment.
-  static std::atomic<int> per_cu{-1};
-  const void *kfn = (const void *)march3d_kernel<T, BOX, R, KL, NW, M, VX, HB, PF, WPE, RAS, HA>;
-  const int64_t slots = resident_wgs(kfn, NW * 64, &per_cu);
-  plan_segments(span, (int64_t)a.ntx * a.nty, &a.zseg, &a.nseg, slots > 0 ? slots * 3 / 2 : kTargetWgs);
-  const int64_t nwg = (int64_t)a.ntx * a.nty * a.nseg;
-  if (nwg > 0x7fffffff) {
-    if (msg) *msg = "grid too large for one launch";
-    return -1;
-  }
-  const int64_t grid = xcd_grid(nwg);
-  hipLaunchKernelGGL((march3d_kernel<T, BOX, R, KL, NW, M, VX, HB, PF, WPE, RAS, HA>), dim3((unsigned)grid), dim3(NW * 64), 0,
-                     stream, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) {
-    if (msg) *msg = std::string("kernel launch: ") + hipGetErrorString(e);
-    return -5;
-  }
-  return 0;
-}
+};
 
 template <typename T, bool BOX, int R, int KL, int VX, int PF, bool ROT, bool RAS = false>
 int launch_march2d_one(const LaunchParams &p, hipStream_t stream, std::string *msg) {
@@ -241,25 +261,42 @@ constexpr size_t march_lds() {
   return sizeof(A) * KL * HB * NW * 2 * R * 64 * VX;
 }
 
-// Kernel choice per depth, from measurements on MI355X (one launch over a
-// 2048x1024x80 FP32 chunk; all variants give identical bits):
-//   * single-step launches run best with 1 KiB rows (4 cells per lane, 16
-//     waves of 2 rows): 0.32 ms, 4.1 TB/s;
+// Last-level cache of MI355X: a launch whose planes read and written fit it
+// is bound by its march steps, a larger one by HBM.
+constexpr uint64_t kLastLevelCache = (uint64_t)256 << 20;
+
+// Kernel choice per depth, from measurements on MI355X (all variants give
+// identical bits).
+//
+// 3D launches that stream from HBM (2048x1024x80 FP32 chunks) use wide rows:
+//   * single-step launches 1 KiB rows (4 cells per lane, 16 waves of 2 rows):
+//     0.26 ms, where one cell per lane takes 0.35;
 //   * two fused steps of the radius-1 star: 1 KiB rows, 8 waves of 4 rows
-//     (0.28 ms, 4.6 TB/s);
+//     (0.26 ms against 0.35);
 //   * three fused steps of the radius-1 star and two of the radius-2 star:
-//     512-byte rows, 8 waves of 6 rows (taller tiles re-read fewer halo rows;
-//     1.37 and 0.82 T updates/s);
+//     512-byte rows, 8 waves of 6 rows (0.28 against 0.38 ms for the former;
+//     taller tiles re-read fewer halo rows);
 //   * other deeper fusion and the 27-point box: 512-byte rows, 8 waves of 4
-//     rows (27-point at 2 levels 0.70 T updates/s);
-//   (the taller shapes hold FP32 sums only: FP64 keeps the 4-row tiles)
-//   * grids whose row length is not a multiple of the cells per lane fall
-//     back to the register-column kernel, 2D grids and whatever does not fit
-//     to the LDS-plane kernel.
+//     rows (27-point at 2 levels 0.36 against 0.40 ms);
+//   (the taller shapes hold FP32 sums only: FP64 keeps the 4-row tiles).
+// Launches that fit the last-level cache, and rows that are not whole vectors,
+// use the narrow shape: one cell per lane, 8 waves of 4 rows.  Its tiles are a
+// third to a sixth of the wide ones', so a mid-size grid divides evenly over
+// the CUs, several workgroups share a CU and hide each other's barriers, and
+// the tile overhang past the grid is smaller: 3 levels of the 7-point star on
+// 256^3 44 us against 50 in the wide shape, 512x512x128 68 against 85,
+// 96x40x48 9 against 15; two levels of the BF16 13-point star on 320x320x26
+// 19 against 23.  The cost model prices the wide shapes 20 % too low against
+// the narrow one (their two waves per SIMD issue at 66 of the 73 TFLOP/s that
+// four reach), hence the factor.  Odd rows: the 27-point box on 301x257x203,
+// two levels, 62 us, 85 in the register-column kernel that took them before.
+// 2D grids whose rows are not whole vectors, and planes of 4 GiB or more, take
+// the LDS-plane kernel.
 template <typename T, int NDIM, bool BOX, int R, int KL, bool RAS>
 int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
   using A = typename Store<T>::A;
   constexpr size_t kLdsMax = 160 * 1024;
+  if (p.out_hi <= p.out_lo) return 0;
   if constexpr (NDIM == 2) {
     // unrolling by the stencil width is kept while the unrolled body stays
     // within a few thousand FMAs
@@ -267,10 +304,12 @@ int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
     if (march_fits<T, 4>(p)) return launch_march2d_one<T, BOX, R, KL, 4, 2, rot, RAS>(p, s, msg);
   }
   if constexpr (NDIM == 3) {
-    constexpr bool wide = KL == 1 && march_lds<A, KL, 16, R, 4, 2>() <= kLdsMax;
+    constexpr bool single = KL == 1 && march_lds<A, KL, 16, R, 4, 2>() <= kLdsMax;
     constexpr bool a32 = sizeof(A) == 4;
     constexpr bool square = a32 && !BOX && R == 1 && KL == 2;
     constexpr bool tall = a32 && !BOX && ((R == 1 && KL == 3) || (R == 2 && KL == 2));
+    // FP64 sums of two levels at radius 2 would spill in any wide shape
+    constexpr bool no_wide = !a32 && R == 2 && KL == 2;
     constexpr int HB = march_lds<A, KL, 8, R, 2, 2>() <= 65536 ? 2 : 1;
     // Star tiles of 1 KiB FP32 rows (2 KiB FP64) take a 64-byte x halo: each
     // output row is then whole 128-byte lines.  Measured on 2048x1024
@@ -280,26 +319,31 @@ int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
     // 512-byte-row shapes of deeper fusion and the 27-point box lose more to
     // the wider halo's arithmetic than they gain; 16-bit rows gain nothing.
     constexpr int HA4 = BOX ? 4 : sizeof(T) == 4 ? 16 : sizeof(T) == 8 ? 8 : 4;
-    if constexpr (wide) {
-      if (march_fits<T, 4>(p)) return launch_march_one<T, BOX, R, KL, 16, 2, 4, 2, 2, 1, RAS, HA4>(p, s, msg);
-    } else {
-      if constexpr (square)
-        if (march_fits<T, 4>(p)) return launch_march_one<T, BOX, R, KL, 8, 4, 4, 2, 2, 1, RAS, HA4>(p, s, msg);
-      if constexpr (tall)
-        if (march_fits<T, 2>(p)) return launch_march_one<T, BOX, R, KL, 8, 6, 2, 2, 2, 1, RAS>(p, s, msg);
-      if constexpr (march_lds<A, KL, 8, R, 2, HB>() <= kLdsMax && 2 * ((KL * R + 1) / 2) < 32 &&
-                    4 >= R && 32 > 2 * KL * R)
-        if (march_fits<T, 2>(p)) return launch_march_one<T, BOX, R, KL, 8, 4, 2, HB, 2, 1, RAS>(p, s, msg);
+    constexpr int VXW = single || square ? 4 : 2;
+    constexpr int NWW = single ? 16 : 8, MW = single ? 2 : tall ? 6 : 4;
+    constexpr int HBW = single || square || tall ? 2 : HB, HAW = single || square ? HA4 : VXW;
+    using Narrow = March3d<T, BOX, R, KL, 8, 4, 1, 2, 2, 1, RAS>;
+    if (march_fits<T, 1>(p)) {
+      const uint64_t moved = (uint64_t)(std::min(p.in_hi, p.n_axis) - std::max<int64_t>(p.in_lo, 0) + p.out_hi - p.out_lo) *
+                             (uint64_t)p.plane * sizeof(T);
+      const bool streams = moved > kLastLevelCache;
+      if constexpr (!no_wide) {
+        using Wide = March3d<T, BOX, R, KL, NWW, MW, VXW, HBW, 2, 1, RAS, HAW>;
+        if (march_fits<T, VXW>(p)) {
+          const MarchPlan w = Wide::plan(p);
+          if (streams) return Wide::launch(p, w, s, msg);
+          const MarchPlan n = Narrow::plan(p);
+          return w.cost < 0.8 * n.cost ? Wide::launch(p, w, s, msg) : Narrow::launch(p, n, s, msg);
+        }
+        if constexpr (square) {   // rows of an odd number of 2-cell vectors
+          using Mid = March3d<T, BOX, R, KL, 8, 4, 2, 2, 2, 1, RAS>;
+          if (streams && march_fits<T, 2>(p)) return Mid::launch(p, Mid::plan(p), s, msg);
+        }
+      }
+      return Narrow::launch(p, Narrow::plan(p), s, msg);
     }
   }
-  constexpr size_t lds1 = sizeof(A) * KL * 1 * 16 * 2 * R * 64 * 4;
-  constexpr size_t ldsn = sizeof(A) * KL * 2 * 4 * 2 * R * 64 * 1;
-  if constexpr (NDIM == 3 && KL == 1 && lds1 <= 65536)
-    return launch_col_one<T, BOX, R, KL, 16, 2, 4, 1, RAS>(p, s, msg);
-  else if constexpr (NDIM == 3 && KL >= 2 && 2 * KL * R < 32 && ldsn <= 65536)
-    return launch_col_one<T, BOX, R, KL, 4, 8, 1, 2, RAS>(p, s, msg);
-  else
-    return launch_one<T, NDIM, BOX, R, KL, RAS>(p, s, msg);
+  return launch_one<T, NDIM, BOX, R, KL, RAS>(p, s, msg);
 }
 
 // Expand one stencil's depths 1..MAXKL into a switch on p.kl.

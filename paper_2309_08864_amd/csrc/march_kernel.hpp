@@ -1,11 +1,11 @@
 // march_kernel.hpp -- fused-step kernel for 3D star and box stencils with the
 // march along the cut axis unrolled by the stencil width.
 //
-// Same contract and the same per-cell arithmetic as tb_kernel and
-// col3d_kernel (each output's FMA chain starts from +0 and runs over the
-// points in lexicographic (dz, dy, dx) order, per-level rounding to storage),
-// so all three give identical bits.  What this one changes is the cost per
-// march step, which decides whether a fused launch keeps up with HBM:
+// Same contract and the same per-cell arithmetic as tb_kernel (each output's
+// FMA chain starts from +0 and runs over the points in lexicographic
+// (dz, dy, dx) order, per-level rounding to storage), so the two give
+// identical bits.  What this one changes is the cost per march step, which
+// decides whether a fused launch keeps up with HBM:
 //   * the 2R+1 partial sums of a cell live in a ring indexed by output plane
 //     modulo 2R+1; the march loop is unrolled by 2R+1 steps, so every ring
 //     index is a compile-time constant and nothing is moved between
@@ -21,7 +21,8 @@
 //   * all march arithmetic on plane indices is 32-bit and uniform, and each
 //     row is addressed as a per-plane base plus one 32-bit byte offset;
 //   * a lane owns VX consecutive x cells (VX = 4: 1 KiB FP32 rows, 16-byte
-//     accesses), a wave M rows, a workgroup NW waves stacked in y; x
+//     accesses; VX = 1: any row length), a wave M rows, a workgroup NW waves
+//     stacked in y; x
 //     neighbours across lanes come from whole-wave DPP shifts, y neighbours
 //     across waves from LDS (HB = 2: double-buffered, one barrier per step;
 //     HB = 1: one buffer and a second barrier before it is overwritten).
@@ -33,7 +34,7 @@
 #pragma once
 #include <utility>
 
-#include "star_kernel.hpp"
+#include "lane_tile.hpp"
 
 namespace so2dr {
 

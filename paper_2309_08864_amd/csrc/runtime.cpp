@@ -609,15 +609,16 @@ int link_probe(void *host_a, void *host_b, void *dev_a, void *dev_b, size_t byte
 }
 
 int launch_tb(int dtype, const LaunchParams &p, hipStream_t stream, std::string *msg) {
-  switch (dtype) {
-    case SO2DR_F32: return launch_tb_f32(p, stream, msg);
-    case SO2DR_F64: return launch_tb_f64(p, stream, msg);
-    case SO2DR_BF16: return launch_tb_bf16(p, stream, msg);
-    case SO2DR_F16: return launch_tb_f16(p, stream, msg);
-    default:
-      if (msg) *msg = "unknown storage type";
-      return SO2DR_E_INVALID;
+  using Fn = int (*)(const LaunchParams &, hipStream_t, std::string *);
+  static constexpr Fn table[4][3] = {{launch_tb_0_0, launch_tb_0_1, launch_tb_0_2},
+                                     {launch_tb_1_0, launch_tb_1_1, launch_tb_1_2},
+                                     {launch_tb_2_0, launch_tb_2_1, launch_tb_2_2},
+                                     {launch_tb_3_0, launch_tb_3_1, launch_tb_3_2}};
+  if (dtype < 0 || dtype > 3) {
+    if (msg) *msg = "unknown storage type";
+    return SO2DR_E_INVALID;
   }
+  return table[dtype][stencil_group(p.stencil)](p, stream, msg);
 }
 
 }  // namespace so2dr

@@ -115,11 +115,16 @@ struct AdjCtx {
 // What a copy-out on s_out needs before it is queued: the chunk's compute
 // event, waited for by the host where the copy is the runtime's (as in the
 // forward executor, whose header says why), by the stream otherwise.
-static int out_after(const AdjCtx &C, hipEvent_t comp, bool host) {
-  if (host)
+static int out_after(const Plan &P, const AdjCtx &C, hipEvent_t comp, bool host) {
+  if (host) {
     AHIP(hipEventSynchronize(comp));
-  else
+    if (P.n_slots > 1 && launch_empty(C.s_out)) {
+      set_error("empty kernel launch failed");
+      return SO2DR_E_HIP;
+    }
+  } else {
     AHIP(hipStreamWaitEvent(C.s_out, comp, 0));
+  }
   return SO2DR_OK;
 }
 
@@ -136,7 +141,7 @@ static int loss_pass(Plan &P, AdjCtx &C, void *lam_host, const void *y_host, so2
   auto out = [&](int i) -> int {
     const int64_t z0 = P.bnd[i], z1 = P.bnd[i + 1];
     const size_t n = (size_t)(z1 - z0) * pb;
-    ARC(out_after(C, P.ev_comp[i], hold));
+    ARC(out_after(P, C, P.ev_comp[i], hold));
     ARC(copy_to_host(static_cast<char *>(lam_host) + (size_t)z0 * pb, P.slot_buf(i % P.n_slots, 0), n,
                      lam_host, d_lam, C.s_out));
     AHIP(hipEventRecord(P.ev_d2h[i], C.s_out));
@@ -197,7 +202,7 @@ static int reverse_round(Plan &P, AdjCtx &C, const void *u_host, void *lam_host,
   auto out = [&](int i) -> int {
     const int64_t bz = area_lo(P, i, kp, 0), o0 = area_lo(P, i, kp, kp), o1 = area_hi(P, i, kp, kp);
     const char *src = P.slot_buf(i % P.n_slots, LA) + (size_t)(o0 - bz) * pb;
-    ARC(out_after(C, P.ev_comp[i], hold));
+    ARC(out_after(P, C, P.ev_comp[i], hold));
     ARC(copy_to_host(static_cast<char *>(lam_host) + (size_t)o0 * pb, src, (size_t)(o1 - o0) * pb, lam_host,
                      d_lam, C.s_out));
     AHIP(hipEventRecord(P.ev_d2h[i], C.s_out));

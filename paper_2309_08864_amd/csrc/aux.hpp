@@ -30,4 +30,7 @@ int launch_wgrad(int dtype, const void *lam, const void *u, int64_t buf_z0, int 
 // of `grid` workgroups on stream s.
 int launch_dcopy(void *dst, const void *src, size_t bytes, hipStream_t s, int grid = 1024);
 
+// An empty kernel on stream s (see the executor's header for what it is for).
+int launch_empty(hipStream_t s);
+
 }  // namespace so2dr

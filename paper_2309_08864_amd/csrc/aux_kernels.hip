@@ -52,6 +52,13 @@ int launch_dcopy(void *dst, const void *src, size_t bytes, hipStream_t s, int gr
   return hipGetLastError() == hipSuccess ? 0 : -5;
 }
 
+__global__ __launch_bounds__(64) void empty_kernel() {}
+
+int launch_empty(hipStream_t s) {
+  hipLaunchKernelGGL(empty_kernel, dim3(1), dim3(64), 0, s);
+  return hipGetLastError() == hipSuccess ? 0 : -5;
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void loss_kernel(T *lam_u, const T *y, int64_t n, double *partials) {
   __shared__ double red[kRedThreads];

@@ -26,38 +26,45 @@ __device__ __forceinline__ double dpp_f(double v) {
 }
 
 // VX consecutive stored elements <-> VX values of the accumulation type, in
-// one vector access (the caller guarantees alignment)
+// one vector access.  The address need only be aligned to an element: rows of
+// any length start anywhere, and the memory path takes such accesses whole.
 template <typename T, int VX> struct VecIO;
 template <int VX> struct VecIO<float, VX> {
   using V = typename std::conditional<VX == 4, float4, float2>::type;
   static __device__ __forceinline__ void load(const float *p, float *v) {
-    const V q = *reinterpret_cast<const V *>(p);
+    V q;
+    __builtin_memcpy(&q, p, sizeof(V));
     __builtin_memcpy(v, &q, sizeof(V));
   }
   static __device__ __forceinline__ void store(float *p, const float *v) {
     V q;
     __builtin_memcpy(&q, v, sizeof(V));
-    *reinterpret_cast<V *>(p) = q;
+    __builtin_memcpy(p, &q, sizeof(V));
   }
 };
 template <int VX> struct VecIO<double, VX> {
   static __device__ __forceinline__ void load(const double *p, double *v) {
 #pragma unroll
     for (int i = 0; i < VX; i += 2) {
-      const double2 q = reinterpret_cast<const double2 *>(p)[i / 2];
+      double2 q;
+      __builtin_memcpy(&q, p + i, sizeof(q));
       v[i] = q.x;
       v[i + 1] = q.y;
     }
   }
   static __device__ __forceinline__ void store(double *p, const double *v) {
 #pragma unroll
-    for (int i = 0; i < VX; i += 2) reinterpret_cast<double2 *>(p)[i / 2] = make_double2(v[i], v[i + 1]);
+    for (int i = 0; i < VX; i += 2) {
+      const double2 q = make_double2(v[i], v[i + 1]);
+      __builtin_memcpy(p + i, &q, sizeof(q));
+    }
   }
 };
 template <typename H16, int VX> struct VecIOHalf {
   using V = typename std::conditional<VX == 4, uint2, unsigned>::type;
   static __device__ __forceinline__ void load(const H16 *p, float *v) {
-    const V q = *reinterpret_cast<const V *>(p);
+    V q;
+    __builtin_memcpy(&q, p, sizeof(V));
     unsigned short bits[VX];
     __builtin_memcpy(bits, &q, sizeof(V));
 #pragma unroll
@@ -77,7 +84,7 @@ template <typename H16, int VX> struct VecIOHalf {
     }
     V q;
     __builtin_memcpy(&q, bits, sizeof(V));
-    *reinterpret_cast<V *>(p) = q;
+    __builtin_memcpy(p, &q, sizeof(V));
   }
 };
 template <int VX> struct VecIO<__hip_bfloat16, VX> : VecIOHalf<__hip_bfloat16, VX> {};

@@ -18,8 +18,8 @@ namespace so2dr {
 constexpr int64_t kTargetWgs = 1024;
 constexpr int64_t kMinSegPlanes = 16;
 
-// Segmenting of the cut axis for the LDS-plane kernel and 2D rows: `target`
-// workgroups, never segments shorter than kMinSegPlanes.
+// Segmenting of the cut axis for the LDS-plane kernel: `target` workgroups,
+// never segments shorter than kMinSegPlanes.
 inline void plan_segments(int64_t span, int64_t tiles, int64_t *zseg, int *nseg,
                           int64_t target = kTargetWgs) {
   int64_t n = std::max<int64_t>(1, (target + tiles - 1) / tiles);
@@ -132,14 +132,17 @@ inline bool march_fits(const LaunchParams &p) {
 // `issue` and that of the workgroups sharing its CU, and a segment of zseg
 // output planes takes zseg + extra steps; workgroups run in rounds of CUs x
 // per_cu.  Candidates fill k workgroups per CU, k = 1, 2, ..., which is where
-// the rounds change; more, shorter segments only for a gain of 2 %, since each
-// re-reads `extra` planes.
+// the rounds change; more, shorter segments only for a gain of 0.5 %, since each
+// re-reads `extra` planes.  per_wg: tiles a workgroup takes (2D: one per wave).
 //
 // Measured on MI355X (3D 7-point FP32, 3 levels, tiles of 8 waves x 6 rows x 2
 // cells): a 256^3 grid took 76 us in 336 workgroups of 16-plane segments (the
 // former rule: 1.5 workgroups per slot, segments of at least 16 planes) and
 // 50 us in 252 of 22 planes, one round instead of two; a 320 x 320 x 26 chunk
-// 52 us in 24 workgroups and 19 us in 216.  Over 323 launches of 47 shapes on 9
+// 52 us in 24 workgroups and 19 us in 216.  2D: one level of the radius-3 box on
+// 12800^2 took 329 us in 1027 workgroups, five on some CUs, and 290 us in
+// 1014; five levels of the radius-1 box on 1020 x 767 rows 19 us in 17-row
+// segments and 11 us in 4-row ones.  Over 323 launches of 47 shapes on 9
 // grids the choice came within 3 % (geometric mean) of the best segmenting
 // tried.
 struct MarchPlan {
@@ -149,21 +152,21 @@ struct MarchPlan {
 };
 
 inline MarchPlan plan_march(int64_t span, int64_t tiles, int extra, int cus, int per_cu, double lat,
-                            double issue) {
+                            double issue, int per_wg = 1) {
   constexpr int kMaxPerCu = 12;    // candidates; beyond, rounds no longer matter
   constexpr int kPrologue = 2;     // steps' worth of start-up per workgroup
   MarchPlan best;
   int64_t last = 0;
   for (int k = 1; k <= kMaxPerCu; ++k) {
-    const int64_t want = std::min(span, std::max<int64_t>(1, (int64_t)k * cus / tiles));
+    const int64_t want = std::min(span, std::max<int64_t>(1, (int64_t)k * cus * per_wg / tiles));
     if (want == last) continue;
     last = want;
     const int64_t zseg = (span + want - 1) / want, nseg = (span + zseg - 1) / zseg;
-    const int64_t n = tiles * nseg, full = n / ((int64_t)cus * per_cu), rest = n - full * cus * per_cu;
+    const int64_t n = (tiles * nseg + per_wg - 1) / per_wg, full = n / ((int64_t)cus * per_cu), rest = n - full * cus * per_cu;
     const double t = (double)full * (lat + per_cu * issue) +
                      (rest > 0 ? lat + (double)((rest + cus - 1) / cus) * issue : 0.0);
     const double c = (double)(zseg + extra + kPrologue) * t;
-    if (best.nseg == 0 || c < 0.98 * best.cost) best = {zseg, (int)nseg, c};
+    if (best.nseg == 0 || c < 0.995 * best.cost) best = {zseg, (int)nseg, c};
   }
   return best;
 }
@@ -228,25 +231,25 @@ int launch_march2d_one(const LaunchParams &p, hipStream_t stream, std::string *m
     if (msg) *msg = "weight count does not match the stencil";
     return -1;
   }
-  if (!march_fits<T, VX>(p)) {
-    if (msg) *msg = "launch does not fit the march kernel's layout";
-    return -1;
-  }
   TbArgs<A> a = launch_args<A>(p, S::npts());
   a.ntx = (int)((p.nx + G::OX - 1) / G::OX);
   a.nty = 1;
-  const int64_t span = p.out_hi - p.out_lo;
-  if (span <= 0) return 0;
-  // one wave per (tile, segment); aim for 4 waves per targeted workgroup
-  plan_segments(span, ((int64_t)a.ntx + 3) / 4, &a.zseg, &a.nseg);
-  const int64_t tasks = (int64_t)a.ntx * a.nseg;
-  const int64_t nwg = (tasks + 3) / 4;
-  if (nwg > 0x7fffffff / 4) {
+  const auto kernel = march2d_kernel<T, BOX, R, KL, VX, PF, ROT, RAS>;
+  static std::atomic<int> per_cu{-1};
+  const int64_t slots = resident_wgs((const void *)kernel, 64 * kRowWaves, &per_cu);
+  const int occ = std::max(1, per_cu.load(std::memory_order_relaxed));
+  // a wave's instructions per row (as for the 3D shapes) at 4 cycles each
+  constexpr double issue = 4.0 * (KL * (VX * S::npts() + 4.0) + 10.0), lat = 0.3 * issue;
+  const MarchPlan mp = plan_march(p.out_hi - p.out_lo, a.ntx, 2 * KL * R + KL - 1, slots > 0 ? (int)(slots / occ) : 256,
+                                  occ, lat, issue, kRowWaves);
+  a.zseg = mp.zseg;
+  a.nseg = mp.nseg;
+  const int64_t nwg = ((int64_t)a.ntx * a.nseg + kRowWaves - 1) / kRowWaves;
+  if (nwg > 0x7fffffff / kRowWaves) {
     if (msg) *msg = "grid too large for one launch";
     return -1;
   }
-  const int64_t grid = xcd_grid(nwg);
-  hipLaunchKernelGGL((march2d_kernel<T, BOX, R, KL, VX, PF, ROT, RAS>), dim3((unsigned)grid), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)xcd_grid(nwg)), dim3(64 * kRowWaves), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     if (msg) *msg = std::string("kernel launch: ") + hipGetErrorString(e);
@@ -290,18 +293,23 @@ constexpr uint64_t kLastLevelCache = (uint64_t)256 << 20;
 // the narrow one (their two waves per SIMD issue at 66 of the 73 TFLOP/s that
 // four reach), hence the factor.  Odd rows: the 27-point box on 301x257x203,
 // two levels, 62 us, 85 in the register-column kernel that took them before.
-// 2D grids whose rows are not whole vectors, and planes of 4 GiB or more, take
-// the LDS-plane kernel.
+// Planes of 4 GiB or more (and 2D rows of 4 GiB) take the LDS-plane kernel.
 template <typename T, int NDIM, bool BOX, int R, int KL, bool RAS>
 int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
   using A = typename Store<T>::A;
   constexpr size_t kLdsMax = 160 * 1024;
   if (p.out_hi <= p.out_lo) return 0;
   if constexpr (NDIM == 2) {
-    // unrolling by the stencil width is kept while the unrolled body stays
-    // within a few thousand FMAs
-    constexpr bool rot = (int64_t)KL * 4 * Stencil<2, BOX, R>::npts() * (2 * R + 1) > 2400;
-    if (march_fits<T, 4>(p)) return launch_march2d_one<T, BOX, R, KL, 4, 2, rot, RAS>(p, s, msg);
+    // Unrolling by the stencil width is kept while the unrolled body stays
+    // within 3000 FMAs (12 KiB of code; 2400 in FP64, whose FMAs take twice the
+    // code): one level of the radius-4 box, 2916
+    // of them, takes 464 us on 12800^2 unrolled and 489 us with shifting sums.
+    // FP64 lanes own two cells: four need 158 registers at 4 levels, three
+    // waves per SIMD, and 93 us on 4800^2 where two need 82; two levels of the
+    // radius-3 box gain 10 %.
+    constexpr int VX = sizeof(T) == 8 ? 2 : 4;
+    constexpr bool rot = (int64_t)KL * VX * Stencil<2, BOX, R>::npts() * (2 * R + 1) > (sizeof(T) == 8 ? 2400 : 3000);
+    if (march_fits<T, 1>(p)) return launch_march2d_one<T, BOX, R, KL, VX, 2, rot, RAS>(p, s, msg);
   }
   if constexpr (NDIM == 3) {
     constexpr bool single = KL == 1 && march_lds<A, KL, 16, R, 4, 2>() <= kLdsMax;

@@ -18,18 +18,28 @@
 //     at depth), the sums shift by one register per row instead (ROT = true)
 //     and the march is unrolled only by the prefetch ring's width;
 //   * input rows are prefetched PF rows ahead into a ring of the same width,
-//     unconditionally: the row index is clamped into the buffer's valid rows
-//     and ghost columns read a clamped or wrapped in-grid address; ghosts are
-//     zeroed in a second copy of the march that only waves touching a
-//     Dirichlet boundary run.
-// Requirements checked by the launcher: nx % VX == 0, row bytes and row
-// indices within 32 bits.  Rows outside [in_lo, in_hi) but inside the grid
+//     unconditionally: the row index is clamped into the buffer's valid rows;
+//   * rows may have any length: loads and stores are whole vectors aligned to
+//     an element only, and a tile that reaches past the right end of a row
+//     that is not whole vectors starts up to VX - 1 cells further left, so
+//     that a lane ends where the row does (the few cells it shares with its
+//     neighbour are written twice, with the same value).  Three copies of the
+//     march: inside the grid; at an end of the row or of the march, where a
+//     lane reads one clamped or wrapped in-grid address and ghosts are zeroed;
+//     and for a tile that reaches past both ends of such a row, cell by cell.
+//     The middle copy costs as little as the first: in a launch of one round
+//     its waves would otherwise end last (with cell loads there, five levels
+//     of the radius-1 box on 12800^2 took 367 us instead of 306).
+// Requirements checked by the launcher: row bytes and row indices within 32
+// bits.  Rows outside [in_lo, in_hi) but inside the grid
 // hold stale values here rather than zeros: only outputs outside the compute
 // area, which are never stored, depend on them.
 #pragma once
 #include "march_kernel.hpp"
 
 namespace so2dr {
+
+constexpr int kRowWaves = 4;  // one per SIMD of a CU
 
 template <int R, int KL, int VX>
 struct RowTile {
@@ -39,8 +49,10 @@ struct RowTile {
   static_assert(R <= 2 * VX && OX > 0, "tile too small for this depth");
 };
 
-template <typename T, bool BOX, int R, int KL, int VX, int PF, bool ROT, bool RAS, bool GH>
-__device__ __forceinline__ void march2d_tile(const TbArgs<typename Store<T>::A> &a, int lane, int tx_i,
+enum { kInside = 0, kEdge = 1, kEdgeCells = 2 };
+
+template <typename T, bool BOX, int R, int KL, int VX, int PF, bool ROT, bool RAS, int EDGE>
+__device__ __forceinline__ void march2d_tile(const TbArgs<typename Store<T>::A> &a, int lane, int x_lo,
                                              int zo0, int zo1) {
   using A = typename Store<T>::A;
   using S = Stencil<2, BOX, R>;
@@ -54,14 +66,23 @@ __device__ __forceinline__ void march2d_tile(const TbArgs<typename Store<T>::A> 
   T *__restrict__ out = static_cast<T *>(a.out);
 
   const int cx0 = lane * VX;
-  const int gx0 = tx_i * G::OX - G::HX + cx0;  // VX-aligned
-  int lx = gx0;
-  bool keep = true;
-  if (gx0 < 0 || gx0 >= a.nx) {
-    if (a.per_x) lx = ((gx0 % a.nx) + a.nx) % a.nx; else { lx = 0; keep = false; }
+  const int gx0 = x_lo + cx0;
+  // per vector, or per cell in the last copy: byte offset of its (clamped or
+  // wrapped) column, whether it is in the grid, whether this tile stores it
+  constexpr int NV = EDGE == kEdgeCells ? VX : 1;
+  uint32_t boff[NV];
+  bool keep[NV], st[NV];
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int gx = gx0 + j;
+    int lx = gx;
+    keep[j] = true;
+    if (EDGE && (gx < 0 || gx >= a.nx)) {
+      if (a.per_x) lx = ((gx % a.nx) + a.nx) % a.nx; else { lx = 0; keep[j] = false; }
+    }
+    boff[j] = (uint32_t)lx * (uint32_t)sizeof(T);
+    st[j] = cx0 >= G::HX && cx0 < G::TX - G::HX && (!EDGE || gx < a.nx);
   }
-  const bool st = cx0 >= G::HX && cx0 < G::TX - G::HX && gx0 < a.nx;
-  const uint32_t boff = (uint32_t)lx * (uint32_t)sizeof(T);
 
   constexpr int NR = ROT ? PF + 1 : W;  // input ring slots: row P0 + p in slot p mod NR
   constexpr int U = NR;                 // rows per unrolled group
@@ -83,7 +104,12 @@ __device__ __forceinline__ void march2d_tile(const TbArgs<typename Store<T>::A> 
   auto load_row = [&](int p, A *dst) {
     const int pc = min(max(p, p_lo), p_hi);
     const char *base = reinterpret_cast<const char *>(in + (int64_t)(pc - (int)a.buf_z0) * a.plane);
-    VecIO<T, VX>::load(reinterpret_cast<const T *>(base + boff), dst);
+    if constexpr (EDGE != kEdgeCells) {
+      VecIO<T, VX>::load(reinterpret_cast<const T *>(base + boff[0]), dst);
+    } else {
+#pragma unroll
+      for (int j = 0; j < VX; ++j) dst[j] = Store<T>::load(reinterpret_cast<const T *>(base + boff[j]));
+    }
   };
 #pragma unroll
   for (int k = 0; k < PF; ++k) load_row(P0 + k, ring[k]);
@@ -92,10 +118,10 @@ __device__ __forceinline__ void march2d_tile(const TbArgs<typename Store<T>::A> 
     constexpr int PH = decltype(ph_c)::value;  // s mod U
     constexpr int CUR = PH % NR;                // ring slot consumed now
     load_row(P0 + s + PF, ring[(PH + PF) % NR]);
-    if constexpr (GH) {
+    if constexpr (EDGE != kInside) {
       const bool zg = P0 + s < 0 || P0 + s >= n_axis;
 #pragma unroll
-      for (int j = 0; j < VX; ++j) ring[CUR][j] = keep && !zg ? ring[CUR][j] : A(0);
+      for (int j = 0; j < VX; ++j) ring[CUR][j] = keep[j % NV] && !zg ? ring[CUR][j] : A(0);
     }
     unroll_seq(
         [&](auto li) {
@@ -136,17 +162,23 @@ __device__ __forceinline__ void march2d_tile(const TbArgs<typename Store<T>::A> 
               for (int k = 2 * R; k > 0; --k) acc[l - 1][j][k] = acc[l - 1][j][k - 1];
             }
           }
-          if constexpr (GH) {
+          if constexpr (EDGE != kInside) {
             const bool zg = q < 0 || q >= n_axis;
 #pragma unroll
-            for (int j = 0; j < VX; ++j) res[j] = keep && !zg ? res[j] : A(0);
+            for (int j = 0; j < VX; ++j) res[j] = keep[j % NV] && !zg ? res[j] : A(0);
           }
           if constexpr (l < KL) {
 #pragma unroll
             for (int j = 0; j < VX; ++j) done[l][j] = res[j];
-          } else if (st && q >= zo0 && q < zo1) {
+          } else if (st[0] && q >= zo0 && q < zo1) {
             char *dst = reinterpret_cast<char *>(out + (int64_t)(q - (int)a.out_z0) * a.plane);
-            VecIO<T, VX>::store(reinterpret_cast<T *>(dst + boff), res);
+            if constexpr (EDGE != kEdgeCells) {
+              VecIO<T, VX>::store(reinterpret_cast<T *>(dst + boff[0]), res);
+            } else {
+#pragma unroll
+              for (int j = 0; j < VX; ++j)
+                if (st[j]) Store<T>::store(reinterpret_cast<T *>(dst + boff[j]), res[j]);
+            }
           }
         },
         std::make_integer_sequence<int, KL>{});
@@ -155,31 +187,38 @@ __device__ __forceinline__ void march2d_tile(const TbArgs<typename Store<T>::A> 
     unroll_seq([&](auto ph) { step(ph, s + decltype(ph)::value); }, std::make_integer_sequence<int, U>{});
 }
 
-// 4 independent waves per workgroup; wave task = (tile, segment).  RAS (round
+// kRowWaves independent waves per workgroup; wave task = (tile, segment).  RAS (round
 // at store): levels below the last keep FP32 sums; only the value a launch
 // stores is rounded to the storage type.
 template <typename T, bool BOX, int R, int KL, int VX, int PF, bool ROT, bool RAS = false>
-__global__ __launch_bounds__(256) void march2d_kernel(const TbArgs<typename Store<T>::A> a) {
+__global__ __launch_bounds__(64 * kRowWaves) void march2d_kernel(const TbArgs<typename Store<T>::A> a) {
   using G = RowTile<R, KL, VX>;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ntask = a.ntx * a.nseg;
-  const int wg = xcd_tile(blockIdx.x, (ntask + 3) / 4);
+  const int wg = xcd_tile(blockIdx.x, (ntask + kRowWaves - 1) / kRowWaves);
   if (wg < 0) return;
-  const int task = wg * 4 + wave;
+  const int task = wg * kRowWaves + wave;
   if (task >= ntask) return;
   const int tx_i = task % a.ntx, seg = task / a.ntx;
   const int zo0 = (int)a.out_lo + seg * (int)a.zseg;
   if (zo0 >= (int)a.out_hi) return;
   const int zo1 = min(zo0 + (int)a.zseg, (int)a.out_hi);
-  const int x_lo = tx_i * G::OX - G::HX;
+  int x_lo = tx_i * G::OX - G::HX;
+  const int over = a.nx % VX;   // cells of the row's last, partial vector
+  bool cells = false;
+  if (over != 0 && x_lo + G::TX > a.nx) {
+    cells = x_lo < VX;
+    if (!cells) x_lo -= VX - over;
+  }
   const int P0 = zo0 - KL * R, n_load = zo1 - zo0 + 2 * KL * R;
-  const bool ghosts = (!a.per_x && (x_lo < 0 || x_lo + G::TX > a.nx)) || P0 - 2 * R < 0 ||
-                      P0 + n_load + R > (int)a.n_axis;
-  if (ghosts)
-    march2d_tile<T, BOX, R, KL, VX, PF, ROT, RAS, true>(a, lane, tx_i, zo0, zo1);
+  const bool edge = x_lo < 0 || x_lo + G::TX > a.nx || P0 - 2 * R < 0 || P0 + n_load + R > (int)a.n_axis;
+  if (!edge)
+    march2d_tile<T, BOX, R, KL, VX, PF, ROT, RAS, kInside>(a, lane, x_lo, zo0, zo1);
+  else if (!cells)
+    march2d_tile<T, BOX, R, KL, VX, PF, ROT, RAS, kEdge>(a, lane, x_lo, zo0, zo1);
   else
-    march2d_tile<T, BOX, R, KL, VX, PF, ROT, RAS, false>(a, lane, tx_i, zo0, zo1);
+    march2d_tile<T, BOX, R, KL, VX, PF, ROT, RAS, kEdgeCells>(a, lane, x_lo, zo0, zo1);
 }
 
 }  // namespace so2dr

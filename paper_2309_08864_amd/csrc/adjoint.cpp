@@ -60,32 +60,6 @@ static int ensure(std::vector<hipEvent_t> &v, size_t n) {
   return SO2DR_OK;
 }
 
-// Offsets of the plan's stencil in lexicographic order, in the internal
-// (cut axis, in-plane y, x) frame: a 2D stencil's (dy, dx) acts as (dz, 0, dx).
-static RedOffsets internal_offsets(const Plan &P, int *npts) {
-  RedOffsets o;
-  std::memset(&o, 0, sizeof(o));
-  const int r = P.r;
-  int k = 0;
-  for (int a = (P.ndim == 3 ? -r : 0); a <= (P.ndim == 3 ? r : 0); ++a)
-    for (int b = -r; b <= r; ++b)
-      for (int c = -r; c <= r; ++c) {
-        const int nz = (a != 0) + (b != 0) + (c != 0);
-        if (P.shape == SO2DR_STAR && nz > 1) continue;
-        if (P.ndim == 3) {
-          o.dz[k] = (int8_t)a;
-          o.dy[k] = (int8_t)b;
-        } else {
-          o.dz[k] = (int8_t)b;
-          o.dy[k] = 0;
-        }
-        o.dx[k] = (int8_t)c;
-        ++k;
-      }
-  *npts = k;
-  return o;
-}
-
 static LaunchParams base_launch(const Plan &P, const double *w) {
   LaunchParams lp;
   std::memset(&lp, 0, sizeof(lp));
@@ -108,8 +82,6 @@ struct AdjCtx {
   size_t field = 0;
   double *partials, *acc_w, *acc_loss;
   std::vector<double> wT;  // reflected weights
-  RedOffsets offs;
-  int npts;
 };
 
 // What a copy-out on s_out needs before it is queued: the chunk's compute
@@ -231,52 +203,64 @@ static int reverse_round(Plan &P, AdjCtx &C, const void *u_host, void *lam_host,
     hipStream_t s = C.s_comp;
     AHIP(hipStreamWaitEvent(s, P.ev_h2d[i], 0));
     if (i > 0) AHIP(hipStreamWaitEvent(s, P.ev_rs[i - 1], 0));
+    ShareArgs sh = {};
     for (int f = 0; f < 2; ++f) {
       const int which = f == 0 ? U0 : LA;
-      // copy kernels on the compute stream, as in the forward executor
-      if ((i > 0 && launch_dcopy(at(which, b0 - h), P.rs_pool(f), (size_t)h * pb, s)) ||
-          (i < P.d - 1 && launch_dcopy(P.rs_pool(f), at(which, b1 - h), (size_t)h * pb, s))) {
-        set_error("region-sharing copy kernel launch failed");
-        return SO2DR_E_HIP;
-      }
+      sh.pool[f] = P.rs_pool(f);
+      if (i > 0) sh.halo[f] = at(which, b0 - h);
+      if (i < P.d - 1) sh.top[f] = at(which, b1 - h);
       S->bytes_d2d += (size_t)h * pb * ((i > 0) + (i < P.d - 1));
+    }
+    // a kernel on the compute stream, as in the forward executor
+    if (launch_share(sh, (size_t)h * pb, s)) {
+      set_error("region-sharing copy kernel launch failed");
+      return SO2DR_E_HIP;
     }
     AHIP(hipEventRecord(P.ev_rs[i], s));
     const int64_t own_lo = i == 0 ? 0 : b0 - (int64_t)P.r * kp;
     const int64_t own_hi = i == P.d - 1 ? P.N : b1 - (int64_t)P.r * kp;
     int lcur = LA, lnext = LB;
+    // levels of u that the two recompute buffers hold (-1: none).  A level is
+    // advanced from the highest one held below it; the intermediate ones that
+    // a run of launches leaves behind serve the next, lower levels: 8
+    // launches instead of 12 for a round of 8 steps at k_on = 3, 21 instead
+    // of 45 for one of 16.
+    int held[2] = {-1, -1};   // of UA, UB
     for (int st = 0; st < kp; ++st) {
       const int m = kp - 1 - st;  // u level paired with lambda level st
-      int ubuf = U0;
-      if (m > 0) {  // recompute u level m from the round-start state
-        int src = U0, dst = UA, done = 0;
-        while (done < m) {
-          const int kl = std::min(P.k_on, m - done);
-          LaunchParams lp = fwd;
-          lp.kl = kl;
-          lp.in = buf(src);
-          lp.out = buf(dst);
-          lp.buf_z0 = bz;
-          lp.out_z0 = bz;
-          lp.in_lo = area_lo(P, i, kp, done);
-          lp.in_hi = area_hi(P, i, kp, done);
-          lp.out_lo = area_lo(P, i, kp, done + kl);
-          lp.out_hi = area_hi(P, i, kp, done + kl);
-          const int rc = launch_tb(P.dtype, lp, s, &msg);
-          if (rc) {
-            set_error(msg);
-            return rc;
-          }
-          S->kernel_launches += 1;
-          done += kl;
-          src = dst;
-          dst = dst == UA ? UB : UA;
+      int src = U0, lvl = 0;
+      for (int k = 0; k < 2; ++k)
+        if (held[k] > lvl && held[k] <= m) {
+          src = UA + k;
+          lvl = held[k];
         }
-        ubuf = src;
+      while (lvl < m) {
+        const int kl = std::min(P.k_on, m - lvl);
+        const int dst = src == UA ? UB : UA;   // levels above m are done with
+        LaunchParams lp = fwd;
+        lp.kl = kl;
+        lp.in = buf(src);
+        lp.out = buf(dst);
+        lp.buf_z0 = bz;
+        lp.out_z0 = bz;
+        lp.in_lo = area_lo(P, i, kp, lvl);
+        lp.in_hi = area_hi(P, i, kp, lvl);
+        lp.out_lo = area_lo(P, i, kp, lvl + kl);
+        lp.out_hi = area_hi(P, i, kp, lvl + kl);
+        const int rc = launch_tb(P.dtype, lp, s, &msg);
+        if (rc) {
+          set_error(msg);
+          return rc;
+        }
+        S->kernel_launches += 1;
+        lvl += kl;
+        src = dst;
+        held[dst - UA] = lvl;
       }
+      const int ubuf = src;
       // dL/dw_k += sum over owned planes of lambda_{t+1}(x) u_t(x + o_k)
-      if (launch_wgrad(P.dtype, buf(lcur), buf(ubuf), bz, (int)P.NX, (int)P.NY, P.per_x, P.per_y, P.N,
-                       own_lo, own_hi, C.offs, C.npts, C.partials, C.acc_w, s)) {
+      if (launch_wgrad(P.dtype, P.stencil, buf(lcur), buf(ubuf), bz, (int)P.NX, (int)P.NY, P.per_x, P.per_y,
+                       P.N, own_lo, own_hi, C.partials, s)) {
         set_error("weight-gradient kernel launch failed");
         return SO2DR_E_HIP;
       }
@@ -378,11 +362,7 @@ static int adjoint_impl(Plan &P, const void *u0, const void *target, void *grad_
   C.acc_w = C.partials + (size_t)kRedWgs * kMaxRedPts;
   C.acc_loss = C.acc_w + 128;
   C.wT.assign(P.weights.rbegin(), P.weights.rend());
-  C.offs = internal_offsets(P, &C.npts);
-  if (C.npts != (int)P.weights.size()) {
-    set_error("internal offset enumeration does not match the weight count");
-    return SO2DR_E_INVALID;
-  }
+  const int npts = (int)P.weights.size();
   AHIP(hipMemsetAsync(C.acc_w, 0, sizeof(double) * 129, C.s_comp));
 
   auto state = [&](int j) -> const void * { return j == 0 ? u0 : ckpt[j - 1]; };
@@ -400,6 +380,9 @@ static int adjoint_impl(Plan &P, const void *u0, const void *target, void *grad_
   if (T == 0) std::memcpy(grad_u0, u0, field);
   // 2. loss and lambda_T
   ARC(loss_pass(P, C, grad_u0, target, &S));
+  // its partial sums are done with: from here they are the weight gradients',
+  // collected over the whole reverse sweep
+  AHIP(hipMemsetAsync(C.partials, 0, sizeof(double) * (size_t)kRedWgs * npts, C.s_comp));
   // 3. reverse, segment by segment
   for (int j = nseg - 1; j >= 0; --j) {
     const int len = std::min(c, T - j * c);
@@ -420,10 +403,14 @@ static int adjoint_impl(Plan &P, const void *u0, const void *target, void *grad_
       ARC(reverse_round(P, C, starts[m], grad_u0, kp, &S));
     }
   }
+  if (launch_wgrad_sum(npts, C.partials, C.acc_w, C.s_comp)) {
+    set_error("weight-gradient sum launch failed");
+    return SO2DR_E_HIP;
+  }
   double host_acc[129];
   AHIP(hipMemcpyAsync(host_acc, C.acc_w, sizeof(host_acc), hipMemcpyDeviceToHost, C.s_comp));
   AHIP(hipStreamSynchronize(C.s_comp));
-  for (int k = 0; k < C.npts; ++k) grad_w[k] = host_acc[k];
+  for (int k = 0; k < npts; ++k) grad_w[k] = host_acc[k];
   *loss = host_acc[128];
   S.wall_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
   S.cell_updates = (uint64_t)P.N * (uint64_t)P.plane * (uint64_t)T;

@@ -6,6 +6,8 @@
 #include <hip/hip_fp16.h>
 
 #include "aux.hpp"
+#include "launch.hpp"
+#include "tb_kernel.hpp"
 #include "../../include/so2dr.h"
 
 namespace so2dr {
@@ -52,6 +54,47 @@ int launch_dcopy(void *dst, const void *src, size_t bytes, hipStream_t s, int gr
   return hipGetLastError() == hipSuccess ? 0 : -5;
 }
 
+// Region sharing of up to two fields in one launch: halo <- pool, then pool <-
+// top, element by element (a lane reads its pool element before it writes it).
+// Four copy launches of 6 MB each took 20 us at chunks of 16 planes of 320^2.
+__global__ __launch_bounds__(256) void share_kernel(ShareArgs a, int64_t n) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    uint4 below[2], above[2];
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      if (a.halo[f]) below[f] = static_cast<const uint4 *>(a.pool[f])[i];
+      if (a.top[f]) above[f] = static_cast<const uint4 *>(a.top[f])[i];
+    }
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      if (a.halo[f]) static_cast<uint4 *>(a.halo[f])[i] = below[f];
+      if (a.top[f]) static_cast<uint4 *>(a.pool[f])[i] = above[f];
+    }
+  }
+}
+
+int launch_share(const ShareArgs &a, size_t bytes, hipStream_t s) {
+  if (bytes == 0) return 0;
+  uintptr_t bits = (uintptr_t)bytes;
+  bool meet = false;   // a chunk whose halo and top planes overlap
+  for (int f = 0; f < 2; ++f) {
+    const char *h = static_cast<const char *>(a.halo[f]), *t = static_cast<const char *>(a.top[f]);
+    if (h || t) bits |= (uintptr_t)a.pool[f] | (uintptr_t)h | (uintptr_t)t;
+    if (h && t) meet = meet || (h < t + bytes && t < h + bytes);
+  }
+  if (bits % 16 == 0 && !meet) {
+    hipLaunchKernelGGL(share_kernel, dim3(1024), dim3(256), 0, s, a, (int64_t)(bytes / 16));
+    return hipGetLastError() == hipSuccess ? 0 : -5;
+  }
+  int rc = 0;
+  for (int f = 0; f < 2; ++f) {
+    if (a.halo[f] && !rc) rc = launch_dcopy(a.halo[f], a.pool[f], bytes, s);
+    if (a.top[f] && !rc) rc = launch_dcopy(a.pool[f], a.top[f], bytes, s);
+  }
+  return rc;
+}
+
 __global__ __launch_bounds__(64) void empty_kernel() {}
 
 int launch_empty(hipStream_t s) {
@@ -84,80 +127,132 @@ __global__ __launch_bounds__(256) void reduce_partials(const double *partials, i
   if (threadIdx.x == 0) acc[k] += t;
 }
 
-// Per workgroup, partials[block * NP + k] = sum over its cells x of
-// lam(x) u(x + o_k).  Workgroups take whole rows of the owned planes in turn
-// (row index -> plane and y once per row, uniform), lanes stride along x, so
-// loads are coalesced and no per-cell division is needed.  A lane loads the
-// values of up to 4 cells of its row (x, x + 256, ...) before it accumulates any,
-// so each wave keeps several cells' loads in flight instead of one's; the
-// accumulation order per lane is unchanged (cells by increasing x, points in
-// order), and neighbours outside the grid are loaded from a clamped in-grid
-// address and not accumulated.
-template <typename T, int NP>
-__global__ __launch_bounds__(256) void wgrad_kernel(const T *lam, const T *u, int64_t buf_z0, int nx,
-                                                    int ny, int per_x, int per_y, int64_t n_axis,
-                                                    int64_t z0, int64_t z1, RedOffsets o,
-                                                    double *partials) {
-  constexpr int WU = NP <= 13 ? 4 : NP <= 27 ? 2 : 1;  // cells per lane in flight
-  __shared__ double red[kRedThreads];
+// Sum over the wave's lanes in a fixed order (rows of 16 lanes by shifts, then
+// the rows); lane 63 holds it.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffLL), CTRL, ROWS, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xF, false);
+  return v + __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v = dpp_add<0x111, 0xF>(v);   // row_shr:1, lanes without a source add 0
+  v = dpp_add<0x112, 0xF>(v);
+  v = dpp_add<0x114, 0xF>(v);
+  v = dpp_add<0x118, 0xF>(v);
+  v = dpp_add<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+  return dpp_add<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+}
+
+// partials[block * NP + k] += sum over the block's cells x of
+// lam(x) u(x + o_k).  A lane takes V consecutive cells of a row (V = 4 where
+// rows are whole vectors, else 1); vectors are dealt to lanes in flat order
+// over the owned planes, and a lane steps from one to its next by carries,
+// without divisions.  Per vector it loads lambda, one vector of u per (dz, dy)
+// row of the stencil and, where the row has x offsets, the R cells on either
+// side, all from clamped in-grid addresses and before any is used; terms whose
+// cell is outside the grid are not accumulated.  Sums stay in the block's own
+// partials from launch to launch; reduce_partials adds the blocks up once.
+//
+// Bound by latency at the gradient's usual chunk sizes (16 planes of 320^2: 14
+// MB from the caches).  One lane per cell of a row with a tree over the
+// workgroup per point and a reduction launch each time took 21 us + 5 us;
+// this takes 7.5 us.
+template <typename T, int NDIM, bool BOX, int R, int V>
+__global__ __launch_bounds__(256) void wgrad_kernel(const T *__restrict__ lam, const T *__restrict__ u,
+                                                    int64_t buf_z0, int nx, int ny, int per_x, int per_y,
+                                                    int64_t n_axis, int64_t z0, int64_t z1, double *partials) {
+  using S = Stencil<NDIM, BOX, R>;
+  constexpr int RY = S::RY, NP = S::npts();
+  __shared__ double red[4][NP];
   double acc[NP];
 #pragma unroll
   for (int k = 0; k < NP; ++k) acc[k] = 0.0;
   const int64_t plane = (int64_t)nx * ny;
-  const int64_t nrows = (z1 - z0) * ny;
-  for (int64_t row = blockIdx.x; row < nrows; row += gridDim.x) {
-    const int64_t z = z0 + row / ny;
-    const int y = (int)(row % ny);
-    const T *lrow = lam + (z - buf_z0) * plane + (int64_t)y * nx;
-    // per point: its row of u (clamped into the grid) and whether that row exists
-    const T *urow[NP];
-    bool row_ok[NP];
+  const uint32_t nv = (uint32_t)nx / V;   // vectors per row (whole)
+  const uint32_t stride = gridDim.x * 256u, q0 = blockIdx.x * 256u + threadIdx.x, nyv = (uint32_t)ny * nv;
+  const int sz = (int)(stride / nyv), sy = (int)(stride % nyv / nv), sx = (int)(stride % nv);
+  int64_t z = z0 + q0 / nyv;
+  int y = (int)(q0 % nyv / nv), xv = (int)(q0 % nv);
+  while (z < z1) {
+    const int x = xv * V;
+    const int64_t at = (z - buf_z0) * plane + (int64_t)y * nx + x;
+    T l[V];
+    T c[2 * R + 1][2 * RY + 1][V];          // the stencil's rows at the lane's cells
+    T e[2 * R + 1][2 * RY + 1][2][R];       // and the R cells left and right of them
+    bool ok[2 * R + 1][2 * RY + 1], okx[2][R];
+    int xe[2][R];
 #pragma unroll
-    for (int k = 0; k < NP; ++k) {
-      int64_t zz = z + o.dz[k];
-      int yy = y + o.dy[k];
-      bool ok = zz >= 0 && zz < n_axis;
-      if (yy < 0 || yy >= ny) {
-        if (per_y) yy = yy < 0 ? yy + ny : yy - ny; else ok = false;
-      }
-      zz = ok ? zz : z;
-      yy = ok ? yy : y;
-      urow[k] = u + (zz - buf_z0) * plane + (int64_t)yy * nx;
-      row_ok[k] = ok;
+    for (int i = 0; i < R; ++i) {
+      const int xl = x - 1 - i, xr = x + V + i;   // e[..][0][i] is x - 1 - i, e[..][1][i] is x + V + i
+      okx[0][i] = per_x || xl >= 0;
+      okx[1][i] = per_x || xr < nx;
+      xe[0][i] = (xl >= 0 ? xl : per_x ? nx - 1 - (-xl - 1) % nx : 0) - x;
+      xe[1][i] = (xr < nx ? xr : per_x ? (xr - nx) % nx : 0) - x;
     }
-    for (int xb = 0; xb < nx; xb += 256 * WU) {
-      T l[WU];
-      T v[WU][NP];
-      bool use[WU][NP];
+    __builtin_memcpy(l, lam + at, sizeof(l));
 #pragma unroll
-      for (int j = 0; j < WU; ++j) {
-        const int x = xb + threadIdx.x + 256 * j;
-        const bool in = x < nx;
-        l[j] = lrow[in ? x : 0];
+    for (int a = -R; a <= R; ++a)
 #pragma unroll
-        for (int k = 0; k < NP; ++k) {
-          int xx = x + o.dx[k];
-          bool ok = in && row_ok[k];
-          if (xx < 0 || xx >= nx) {
-            if (per_x) xx = xx < 0 ? xx + nx : xx - nx; else ok = false;
-          }
-          xx = ok ? xx : 0;
-          v[j][k] = urow[k][xx];
-          use[j][k] = ok;
+      for (int b = -RY; b <= RY; ++b) {
+        if (!S::row_used(a, b)) continue;
+        int yy = y + b;
+        bool in = z + a >= 0 && z + a < n_axis;
+        if (yy < 0 || yy >= ny) {
+          if (per_y) yy = ((yy % ny) + ny) % ny; else in = false;
+        }
+        ok[a + R][b + RY] = in;
+        const T *row = u + at + (in ? a * plane + (int64_t)(yy - y) * nx : 0);
+        __builtin_memcpy(c[a + R][b + RY], row, sizeof(l));
+        if (S::row_has_x(a, b)) {
+#pragma unroll
+          for (int side = 0; side < 2; ++side)
+#pragma unroll
+            for (int i = 0; i < R; ++i) e[a + R][b + RY][side][i] = row[xe[side][i]];
         }
       }
 #pragma unroll
-      for (int j = 0; j < WU; ++j)
+    for (int a = -R; a <= R; ++a)
 #pragma unroll
-        for (int k = 0; k < NP; ++k)
-          if (use[j][k]) acc[k] += to_d(l[j]) * to_d(v[j][k]);
+      for (int b = -RY; b <= RY; ++b) {
+        if (!S::row_used(a, b)) continue;
+        if (!ok[a + R][b + RY]) continue;
+#pragma unroll
+        for (int d = -R; d <= R; ++d) {
+          const int k = S::table.idx[a + R][b + RY][d + R];
+          if (k < 0) continue;
+#pragma unroll
+          for (int j = 0; j < V; ++j) {
+            const int t = j + d;
+            if (t >= 0 && t < V)
+              acc[k] += to_d(l[j]) * to_d(c[a + R][b + RY][t]);
+            else if (okx[t >= V][t < 0 ? -t - 1 : t - V])
+              acc[k] += to_d(l[j]) * to_d(e[a + R][b + RY][t >= V][t < 0 ? -t - 1 : t - V]);
+          }
+        }
+      }
+    xv += sx;
+    y += sy;
+    z += sz;
+    if (xv >= (int)nv) {
+      xv -= (int)nv;
+      ++y;
+    }
+    if (y >= ny) {
+      y -= ny;
+      ++z;
     }
   }
 #pragma unroll
   for (int k = 0; k < NP; ++k) {
-    const double b = block_sum(acc[k], red);
-    if (threadIdx.x == 0) partials[(int64_t)blockIdx.x * NP + k] = b;
+    const double w = wave_sum(acc[k]);
+    if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6][k] = w;
   }
+  __syncthreads();
+  if (threadIdx.x < NP)
+    partials[(int64_t)blockIdx.x * NP + threadIdx.x] +=
+        red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
 }
 
 template <typename T>
@@ -178,42 +273,59 @@ int launch_loss(int dtype, void *lam_u, const void *y, int64_t n, double *partia
   }
 }
 
-template <typename T, int NP>
-static int wgrad_np(const void *lam, const void *u, int64_t buf_z0, int nx, int ny, int per_x, int per_y,
-                    int64_t n_axis, int64_t z0, int64_t z1, const RedOffsets &o, double *partials,
-                    double *acc, hipStream_t s) {
-  hipLaunchKernelGGL((wgrad_kernel<T, NP>), dim3(kRedWgs), dim3(kRedThreads), 0, s,
-                     static_cast<const T *>(lam), static_cast<const T *>(u), buf_z0, nx, ny, per_x,
-                     per_y, n_axis, z0, z1, o, partials);
-  hipLaunchKernelGGL(reduce_partials, dim3(NP), dim3(kRedThreads), 0, s, partials, kRedWgs, NP, acc);
+template <typename T, int NDIM, bool BOX, int R>
+static int wgrad_st(const void *lam, const void *u, int64_t buf_z0, int nx, int ny, int per_x, int per_y,
+                    int64_t n_axis, int64_t z0, int64_t z1, double *partials, hipStream_t s) {
+  // as few passes of kRedWgs workgroups as cover the vectors, evenly filled
+  const int v = nx % 4 == 0 ? 4 : 1;
+  const int64_t need = ((z1 - z0) * ny * (nx / v) + kRedThreads - 1) / kRedThreads;
+  const int64_t passes = (need + kRedWgs - 1) / kRedWgs;
+  const int grid = (int)((need + passes - 1) / passes);
+  const T *l = static_cast<const T *>(lam), *w = static_cast<const T *>(u);
+  if (v == 4)
+    hipLaunchKernelGGL((wgrad_kernel<T, NDIM, BOX, R, 4>), dim3(grid), dim3(kRedThreads), 0, s, l, w, buf_z0, nx, ny,
+                       per_x, per_y, n_axis, z0, z1, partials);
+  else
+    hipLaunchKernelGGL((wgrad_kernel<T, NDIM, BOX, R, 1>), dim3(grid), dim3(kRedThreads), 0, s, l, w, buf_z0, nx, ny,
+                       per_x, per_y, n_axis, z0, z1, partials);
   return hipGetLastError() == hipSuccess ? 0 : SO2DR_E_HIP;
 }
 
 template <typename T>
-static int wgrad_t(const void *lam, const void *u, int64_t buf_z0, int nx, int ny, int per_x, int per_y,
-                   int64_t n_axis, int64_t z0, int64_t z1, const RedOffsets &o, int npts,
-                   double *partials, double *acc, hipStream_t s) {
-#define SO2DR_NP(N) \
-  case N: return wgrad_np<T, N>(lam, u, buf_z0, nx, ny, per_x, per_y, n_axis, z0, z1, o, partials, acc, s);
-  switch (npts) {
-    SO2DR_NP(5) SO2DR_NP(7) SO2DR_NP(9) SO2DR_NP(13) SO2DR_NP(25) SO2DR_NP(27) SO2DR_NP(49) SO2DR_NP(81)
+static int wgrad_t(int stencil, const void *lam, const void *u, int64_t buf_z0, int nx, int ny, int per_x, int per_y,
+                   int64_t n_axis, int64_t z0, int64_t z1, double *partials, hipStream_t s) {
+#define SO2DR_CASE(ID, NDIM, BOX, R) \
+  case ID: return wgrad_st<T, NDIM, BOX, R>(lam, u, buf_z0, nx, ny, per_x, per_y, n_axis, z0, z1, partials, s);
+  switch (stencil) {
+    SO2DR_CASE(ST_2D_STAR_R1, 2, false, 1)
+    SO2DR_CASE(ST_2D_BOX_R1, 2, true, 1)
+    SO2DR_CASE(ST_2D_BOX_R2, 2, true, 2)
+    SO2DR_CASE(ST_2D_BOX_R3, 2, true, 3)
+    SO2DR_CASE(ST_2D_BOX_R4, 2, true, 4)
+    SO2DR_CASE(ST_3D_STAR_R1, 3, false, 1)
+    SO2DR_CASE(ST_3D_STAR_R2, 3, false, 2)
+    SO2DR_CASE(ST_3D_BOX_R1, 3, true, 1)
     default: return SO2DR_E_UNSUPPORTED;
   }
-#undef SO2DR_NP
+#undef SO2DR_CASE
 }
 
-int launch_wgrad(int dtype, const void *lam, const void *u, int64_t buf_z0, int nx, int ny, int per_x,
-                 int per_y, int64_t n_axis, int64_t z0, int64_t z1, const RedOffsets &offs, int npts,
-                 double *partials, double *acc, hipStream_t s) {
+int launch_wgrad(int dtype, int stencil, const void *lam, const void *u, int64_t buf_z0, int nx, int ny, int per_x,
+                 int per_y, int64_t n_axis, int64_t z0, int64_t z1, double *partials, hipStream_t s) {
   if (z1 <= z0) return 0;
   switch (dtype) {
     case SO2DR_F32:
-      return wgrad_t<float>(lam, u, buf_z0, nx, ny, per_x, per_y, n_axis, z0, z1, offs, npts, partials, acc, s);
+      return wgrad_t<float>(stencil, lam, u, buf_z0, nx, ny, per_x, per_y, n_axis, z0, z1, partials, s);
     case SO2DR_F64:
-      return wgrad_t<double>(lam, u, buf_z0, nx, ny, per_x, per_y, n_axis, z0, z1, offs, npts, partials, acc, s);
+      return wgrad_t<double>(stencil, lam, u, buf_z0, nx, ny, per_x, per_y, n_axis, z0, z1, partials, s);
     default:
       return SO2DR_E_UNSUPPORTED;
   }
+}
+
+int launch_wgrad_sum(int npts, const double *partials, double *acc, hipStream_t s) {
+  hipLaunchKernelGGL(reduce_partials, dim3(npts), dim3(kRedThreads), 0, s, partials, kRedWgs, npts, acc);
+  return hipGetLastError() == hipSuccess ? 0 : SO2DR_E_HIP;
 }
 
 }  // namespace so2dr

@@ -360,19 +360,27 @@ int execute(Plan &P, const void *host_in, void *host_out, int steps, so2dr_stats
       case SO2DR_OP_RS_WRITE: {
         const size_t n = (size_t)(op.z1 - op.z0) * pb;
         char *pool = P.rs_pool() + (size_t)op.pool_off * pb;
-        // a copy kernel on the compute stream, not the runtime's copy path,
-        // which may hand device copies to a DMA engine the host copies use
-        int crc;
-        if (op.kind == SO2DR_OP_RS_READ) {
-          char *dst = P.slot_buf(op.slot, op.buf_out) + (size_t)(op.z0 - op.buf_z0) * pb;
-          crc = launch_dcopy(dst, pool, n, s);
-        } else {
-          const char *src = P.slot_buf(op.slot, op.buf_in) + (size_t)(op.z0 - op.buf_z0) * pb;
-          crc = launch_dcopy(pool, src, n, s);
-        }
-        if (crc) {
-          set_error("region-sharing copy kernel launch failed");
-          return SO2DR_E_HIP;
+        // a kernel on the compute stream, not the runtime's copy path, which
+        // may hand device copies to a DMA engine the host copies use; a read
+        // and the write of the same pool planes that follows it share a launch
+        const bool read = op.kind == SO2DR_OP_RS_READ;
+        auto pairs = [&](size_t r) {
+          return r + 1 < ops.size() && ops[r].kind == SO2DR_OP_RS_READ && ops[r + 1].kind == SO2DR_OP_RS_WRITE &&
+                 strm[r] == strm[r + 1] && ops[r].pool_off == ops[r + 1].pool_off && ops[r].slot == ops[r + 1].slot &&
+                 ops[r].z1 - ops[r].z0 == ops[r + 1].z1 - ops[r + 1].z0;
+        };
+        auto slot_planes = [&](const so2dr_op &o) {
+          return P.slot_buf(o.slot, o.kind == SO2DR_OP_RS_READ ? o.buf_out : o.buf_in) + (size_t)(o.z0 - o.buf_z0) * pb;
+        };
+        if (!(read && pairs(k))) {
+          ShareArgs sh = {};
+          sh.pool[0] = pool;
+          if (read) sh.halo[0] = slot_planes(op); else sh.top[0] = slot_planes(op);
+          if (!read && k > 0 && pairs(k - 1)) sh.halo[0] = slot_planes(ops[k - 1]);
+          if (launch_share(sh, n, s)) {
+            set_error("region-sharing copy kernel launch failed");
+            return SO2DR_E_HIP;
+          }
         }
         S.bytes_d2d += n;
         break;

@@ -142,6 +142,9 @@ struct Stencil {
   }
   static constexpr Table table = make();
   static constexpr int npts() { return table.n; }
+  // whether the set has a point on row (dz, dy), and one beside x = 0 there
+  static constexpr bool row_used(int dz, int dy) { return in_set(dz, dy, 0); }
+  static constexpr bool row_has_x(int dz, int dy) { return in_set(dz, dy, 1); }
   // whether any plane uses in-plane offset (dy, dx)
   static constexpr bool used_xy(int dy, int dx) {
     for (int a = -R; a <= R; ++a)

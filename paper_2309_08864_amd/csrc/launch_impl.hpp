@@ -238,8 +238,10 @@ int launch_march2d_one(const LaunchParams &p, hipStream_t stream, std::string *m
   static std::atomic<int> per_cu{-1};
   const int64_t slots = resident_wgs((const void *)kernel, 64 * kRowWaves, &per_cu);
   const int occ = std::max(1, per_cu.load(std::memory_order_relaxed));
-  // a wave's instructions per row (as for the 3D shapes) at 4 cycles each
-  constexpr double issue = 4.0 * (KL * (VX * S::npts() + 4.0) + 10.0), lat = 0.3 * issue;
+  // a wave's instructions per row (as for the 3D shapes) at 4 cycles each; the
+  // latency from launches of 2, 3 and 4 waves per SIMD (12800 x 3260, two
+  // levels of the radius-2 box: 93, 87, 86 us)
+  constexpr double issue = 4.0 * (KL * (VX * S::npts() + 4.0) + 10.0), lat = 900.0;
   const MarchPlan mp = plan_march(p.out_hi - p.out_lo, a.ntx, 2 * KL * R + KL - 1, slots > 0 ? (int)(slots / occ) : 256,
                                   occ, lat, issue, kRowWaves);
   a.zseg = mp.zseg;
@@ -331,7 +333,20 @@ int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
     constexpr int NWW = single ? 16 : 8, MW = single ? 2 : tall ? 6 : 4;
     constexpr int HBW = single || square || tall ? 2 : HB, HAW = single || square ? HA4 : VXW;
     using Narrow = March3d<T, BOX, R, KL, 8, 4, 1, 2, 2, 1, RAS>;
+    // two levels whose halo takes a quarter of 32 rows or whose box costs most
+    // have a taller narrow shape, 8 waves of 6 rows: BF16 13-point on
+    // 301x257x203 52 us against 57, 27-point 59 against 62
+    constexpr bool two_narrow = a32 && KL == 2 && (BOX || R == 2);
+    using Narrow6 = March3d<T, BOX, R, KL, 8, two_narrow ? 6 : 4, 1, 2, 2, 1, RAS>;
     if (march_fits<T, 1>(p)) {
+      auto narrow = [&]() {
+        const MarchPlan n = Narrow::plan(p);
+        if constexpr (two_narrow) {
+          const MarchPlan n6 = Narrow6::plan(p);
+          if (n6.cost < n.cost) return Narrow6::launch(p, n6, s, msg);
+        }
+        return Narrow::launch(p, n, s, msg);
+      };
       const uint64_t moved = (uint64_t)(std::min(p.in_hi, p.n_axis) - std::max<int64_t>(p.in_lo, 0) + p.out_hi - p.out_lo) *
                              (uint64_t)p.plane * sizeof(T);
       const bool streams = moved > kLastLevelCache;
@@ -340,15 +355,16 @@ int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
         if (march_fits<T, VXW>(p)) {
           const MarchPlan w = Wide::plan(p);
           if (streams) return Wide::launch(p, w, s, msg);
-          const MarchPlan n = Narrow::plan(p);
-          return w.cost < 0.8 * n.cost ? Wide::launch(p, w, s, msg) : Narrow::launch(p, n, s, msg);
+          double best = Narrow::plan(p).cost;
+          if constexpr (two_narrow) best = std::min(best, Narrow6::plan(p).cost);
+          return w.cost < 0.8 * best ? Wide::launch(p, w, s, msg) : narrow();
         }
         if constexpr (square) {   // rows of an odd number of 2-cell vectors
           using Mid = March3d<T, BOX, R, KL, 8, 4, 2, 2, 2, 1, RAS>;
           if (streams && march_fits<T, 2>(p)) return Mid::launch(p, Mid::plan(p), s, msg);
         }
       }
-      return Narrow::launch(p, Narrow::plan(p), s, msg);
+      return narrow();
     }
   }
   return launch_one<T, NDIM, BOX, R, KL, RAS>(p, s, msg);

@@ -359,9 +359,9 @@ int make_plan(const so2dr_desc &D, Plan *P) {
     }
     P->k_on = std::min(D.k_on, P->K);
   } else {
-    // the fused depth with the best measured update rate per launch on
+    // the fused depth whose launches update cells fastest as measured on
     // MI355X for this stencil and storage type (rates.hpp): e.g. FP32 3 for
-    // the 7-point star, 2 for the 13-point star and the 27-point box, 8 for
+    // the 7-point star, 2 for the 13-point star and the 27-point box, 7 for
     // the 2D 5-point star, 1 for the widest boxes (bound by arithmetic:
     // fusing only adds tile-edge recomputation)
     const int pref = preferred_depth(P->dtype, P->stencil, P->max_k_on);

@@ -77,22 +77,23 @@ typedef enum { SO2DR_ROUND_EVERY_STEP = 0, SO2DR_ROUND_AT_STORE = 1 } so2dr_roun
 
 /* What carries the host <-> HBM copies (no counterpart in the paper, whose
  * copies are cudaMemcpyAsync).
- *   SO2DR_COPY_DMA: hipMemcpyAsync, the runtime's DMA engines.  Fastest for
- *     large copies (97 GB/s both directions together on MI355X); with many
- *     small copies enqueued at once its rate measured erratic, down to a
- *     third of that.
- *   SO2DR_COPY_KERNEL: a copy kernel of 64 workgroups per copy reads or
- *     writes the page-locked host array through its device mapping (about
- *     85 GB/s both directions together, independent of the copy size); the
- *     host array must be one page-locked allocation mapped into the device,
- *     else the run fails with E_NOT_PINNED.
+ *   SO2DR_COPY_DMA: hipMemcpyAsync, the runtime's DMA engines: 94 GB/s both
+ *     directions together on MI355X in a three-slot sweep of 64 or 32 MiB
+ *     chunks, 84 with 8 MiB, 59 with 2 MiB.
+ *   SO2DR_COPY_KERNEL: a copy kernel per copy reads or writes the page-locked
+ *     host array through its device mapping (61-65 GB/s both directions
+ *     together in those sweeps, 39 with 2 MiB); the host array must be one
+ *     page-locked allocation mapped into the device, else the run fails with
+ *     E_NOT_PINNED.  With one slot the copies and launches of a run share the
+ *     first stream.
  *   SO2DR_COPY_KERNEL_OUT: hipMemcpyAsync host -> HBM, copy kernels
- *     HBM -> host (same requirement on the host arrays).
- *   SO2DR_COPY_AUTO: KERNEL_OUT when the plan's largest chunk copy is
- *     below 512 MiB, a run of T steps queues more than 256 host copies
- *     (2 x chunks x rounds), the plan is not an adjoint plan and both host
- *     arrays are mapped; else DMA (thresholds measured on MI355X; 7-point
- *     2048x1024x1024 at 32 chunks: 88 GB/s KERNEL_OUT, 77 KERNEL, 42 DMA). */
+ *     HBM -> host (same requirement on the host arrays): 82-86 and 43 GB/s.
+ *   SO2DR_COPY_AUTO: KERNEL, all on one stream, when a chunk's planes are at
+ *     most 64 MiB and the plan has one slot, or at most 512 KiB and a run of T
+ *     steps queues at most 256 host copies (2 x chunks x rounds); KERNEL_OUT
+ *     when they are below 512 MiB, more than 256 copies are queued and the
+ *     plan is not an adjoint plan (on one stream too up to 512 KiB); else, and
+ *     where the host arrays are not mapped or are non-coherent, DMA. */
 typedef enum {
   SO2DR_COPY_AUTO = 0,
   SO2DR_COPY_DMA = 1,

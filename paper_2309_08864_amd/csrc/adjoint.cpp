@@ -114,7 +114,7 @@ static int loss_pass(Plan &P, AdjCtx &C, void *lam_host, const void *y_host, so2
     const int64_t z0 = P.bnd[i], z1 = P.bnd[i + 1];
     const size_t n = (size_t)(z1 - z0) * pb;
     ARC(out_after(P, C, P.ev_comp[i], hold));
-    ARC(copy_to_host(static_cast<char *>(lam_host) + (size_t)z0 * pb, P.slot_buf(i % P.n_slots, 0), n,
+    ARC(copy_to_host(P, static_cast<char *>(lam_host) + (size_t)z0 * pb, P.slot_buf(i % P.n_slots, 0), n,
                      lam_host, d_lam, C.s_out));
     AHIP(hipEventRecord(P.ev_d2h[i], C.s_out));
     S->bytes_d2h += n;
@@ -129,8 +129,8 @@ static int loss_pass(Plan &P, AdjCtx &C, void *lam_host, const void *y_host, so2
       if (hold) ARC(out(i - P.n_slots));
       AHIP(hipStreamWaitEvent(C.s_in, P.ev_d2h[i - P.n_slots], 0));
     }
-    ARC(copy_to_device(ub, static_cast<char *>(lam_host) + (size_t)z0 * pb, n, lam_host, d_lam_in, C.s_in));
-    ARC(copy_to_device(yb, static_cast<const char *>(y_host) + (size_t)z0 * pb, n, y_host, d_y, C.s_in));
+    ARC(copy_to_device(P, ub, static_cast<char *>(lam_host) + (size_t)z0 * pb, n, lam_host, d_lam_in, C.s_in));
+    ARC(copy_to_device(P, yb, static_cast<const char *>(y_host) + (size_t)z0 * pb, n, y_host, d_y, C.s_in));
     AHIP(hipEventRecord(P.ev_h2d[i], C.s_in));
     AHIP(hipStreamWaitEvent(C.s_comp, P.ev_h2d[i], 0));
     if (launch_loss(P.dtype, ub, yb, (int64_t)(z1 - z0) * P.plane, C.partials, C.acc_loss, C.s_comp)) {
@@ -175,7 +175,7 @@ static int reverse_round(Plan &P, AdjCtx &C, const void *u_host, void *lam_host,
     const int64_t bz = area_lo(P, i, kp, 0), o0 = area_lo(P, i, kp, kp), o1 = area_hi(P, i, kp, kp);
     const char *src = P.slot_buf(i % P.n_slots, LA) + (size_t)(o0 - bz) * pb;
     ARC(out_after(P, C, P.ev_comp[i], hold));
-    ARC(copy_to_host(static_cast<char *>(lam_host) + (size_t)o0 * pb, src, (size_t)(o1 - o0) * pb, lam_host,
+    ARC(copy_to_host(P, static_cast<char *>(lam_host) + (size_t)o0 * pb, src, (size_t)(o1 - o0) * pb, lam_host,
                      d_lam, C.s_out));
     AHIP(hipEventRecord(P.ev_d2h[i], C.s_out));
     S->bytes_d2h += (size_t)(o1 - o0) * pb;
@@ -193,9 +193,9 @@ static int reverse_round(Plan &P, AdjCtx &C, const void *u_host, void *lam_host,
       AHIP(hipStreamWaitEvent(C.s_in, P.ev_d2h[i - P.n_slots], 0));
     }
     const size_t own = (size_t)(b1 - b0) * pb;
-    ARC(copy_to_device(at(U0, b0), static_cast<const char *>(u_host) + (size_t)b0 * pb, own, u_host, d_u,
+    ARC(copy_to_device(P, at(U0, b0), static_cast<const char *>(u_host) + (size_t)b0 * pb, own, u_host, d_u,
                        C.s_in));
-    ARC(copy_to_device(at(LA, b0), static_cast<char *>(lam_host) + (size_t)b0 * pb, own, lam_host, d_lam_in,
+    ARC(copy_to_device(P, at(LA, b0), static_cast<char *>(lam_host) + (size_t)b0 * pb, own, lam_host, d_lam_in,
                        C.s_in));
     AHIP(hipEventRecord(P.ev_h2d[i], C.s_in));
     S->bytes_h2d += 2 * own;
@@ -344,8 +344,9 @@ static int adjoint_impl(Plan &P, const void *u0, const void *target, void *grad_
   C.kcopy = P.copy_engine == SO2DR_COPY_KERNEL || P.copy_engine == SO2DR_COPY_KERNEL_OUT;
   C.kcopy_in = P.copy_engine == SO2DR_COPY_KERNEL;
   if (C.kcopy) {
-    bool all = mapped_host(u0, field) && mapped_host(target, field) && mapped_host(grad_u0, field);
-    for (int j = 0; j < need; ++j) all = all && mapped_host(ckpt[j], field);
+    auto mapped = [&](const void *p) { return mapped_host(p, field, !P.copy_engine_forced) != nullptr; };
+    bool all = mapped(u0) && mapped(target) && mapped(grad_u0);
+    for (int j = 0; j < need; ++j) all = all && mapped(ckpt[j]);
     if (!all) {
       if (P.copy_engine_forced) {
         set_error("copy kernels need each host array inside one page-locked allocation mapped into the device");
@@ -354,7 +355,7 @@ static int adjoint_impl(Plan &P, const void *u0, const void *target, void *grad_
       C.kcopy = C.kcopy_in = false;
     }
   }
-  const int ns = (int)P.streams.size();
+  const int ns = P.serial && C.kcopy ? 1 : (int)P.streams.size();
   C.s_in = P.streams[0];
   C.s_out = ns >= 2 ? P.streams[1] : P.streams[0];
   C.s_comp = ns >= 3 ? P.streams[2] : P.streams[0];

@@ -30,6 +30,11 @@ int launch_wgrad_sum(int npts, const double *partials, double *acc, hipStream_t 
 // of `grid` workgroups on stream s.
 int launch_dcopy(void *dst, const void *src, size_t bytes, hipStream_t s, int grid = 1024);
 
+// dst <- src, `bytes` bytes at any alignment, one of the two in page-locked host
+// memory (dst where to_host, else src; its device address), by at most `wgs`
+// workgroups.
+int launch_host_copy(void *dst, const void *src, size_t bytes, bool to_host, int wgs, hipStream_t s);
+
 // One region-sharing step of up to two fields: where halo[f] is set, halo[f] <-
 // pool[f]; then, where top[f] is set, pool[f] <- top[f]; `bytes` bytes each.
 struct ShareArgs {

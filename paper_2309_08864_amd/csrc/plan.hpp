@@ -34,6 +34,7 @@ struct Plan {
   int ras = 0;                     // 16-bit storage rounded only where a launch stores
   int copy_engine = SO2DR_COPY_DMA;  // host copies: DMA engines or copy kernels
   bool copy_engine_forced = false;   // chosen by the caller, not automatically
+  bool serial = false;               // copy kernels run on one stream with the launches
   bool lean = false;               // 1 buffer per slot, kernels split into shifted sub-blocks
   int lean_block = 0;              // output planes per sub-block launch
   int64_t lean_extra = 0;          // spare planes below the round-start data
@@ -90,27 +91,36 @@ size_t dtype_size(int dtype);
 int stencil_id(int ndim, int shape, int r);
 int expected_points(int ndim, int shape, int r);
 
-// Automatic copy engine: copy kernels when the largest chunk copy is below
-// kKernelCopyBelow bytes and a run queues more than kKernelCopyQueued host
-// copies at once; the DMA engines otherwise.
+// Automatic copy engine: copy kernels both ways, on one stream with the
+// launches, where the plan has one slot and copies at most kSerialCopyMax bytes
+// per chunk, and with more slots up to kSerialPieceMax; copy kernels out when
+// the largest chunk copy is below kKernelCopyBelow bytes and a run queues more
+// than kKernelCopyQueued host copies at once; the DMA engines otherwise.
+constexpr size_t kSerialCopyMax = (size_t)64 << 20;
+constexpr size_t kSerialPieceMax = (size_t)512 << 10;
 constexpr size_t kKernelCopyBelow = (size_t)512 << 20;
 constexpr int64_t kKernelCopyQueued = 256;
-// Workgroups of one host-copy kernel (about the link's rate per direction).
-constexpr int kHostCopyWgs = 64;
+// Workgroups of one host-copy kernel: the link's rate where nothing runs beside
+// it; a few where the launches and the copies of other slots do, which more of
+// them slow (a 7-point sweep of 512 x 256 x 256 in 16 chunks, copy kernels both
+// ways: 19.0 ms with 8, 22.8 with 32).
+constexpr int kSerialCopyWgs = 32;
+constexpr int kHostCopyWgs = 8;
 
 // Wait for whatever a failed run already queued on the plan's streams
 // (errors ignored; the caller reports the first one).
 void drain_streams(Plan &P);
 
 // Device address of the host range [p, p + bytes) when it lies inside one
-// page-locked allocation mapped into the current device, else null.
-char *mapped_host(const void *p, size_t bytes);
+// page-locked allocation mapped into the current device, else null; with
+// `coherent` also null where the device may cache that memory.
+char *mapped_host(const void *p, size_t bytes, bool coherent = false);
 // One host <-> HBM copy of n bytes on stream s.  With dev_base (the device
 // address of host_base from mapped_host) a copy kernel moves the bytes
 // through the mapping; without, hipMemcpyAsync.  Returns 0 or SO2DR_E_HIP.
-int copy_to_device(void *dst, const void *src_host, size_t n, const void *host_base, char *dev_base,
+int copy_to_device(const Plan &P, void *dst, const void *src_host, size_t n, const void *host_base, char *dev_base,
                    hipStream_t s);
-int copy_to_host(void *dst_host, const void *src, size_t n, const void *host_base, char *dev_base,
+int copy_to_host(const Plan &P, void *dst_host, const void *src, size_t n, const void *host_base, char *dev_base,
                  hipStream_t s);
 
 }  // namespace so2dr

@@ -454,28 +454,42 @@ int make_plan(const so2dr_desc &D, Plan *P) {
   if (P->lean) grow_lean_block(*P);
   P->workspace = ((size_t)P->n_slots * P->bufs_per_slot + (size_t)P->shared_bufs) * P->buf_bytes +
                  (size_t)P->n_rs() * P->rs_bytes + P->scratch_bytes;
-  // Copy engine.  Measured on MI355X with everything enqueued at once, DMA
-  // copies ran at the link's 97 GB/s only while each copy was large; with
-  // smaller copies the rate became erratic (a 64 MiB pattern: 28-82 GB/s
-  // over repeats) while copy kernels held 84-86 GB/s at any size; DMA in with
-  // copy kernels out did best in the executor (the 7-point workload at 32
-  // chunks: 88 GB/s, against 77 with kernels both ways).  Few queued
-  // copies stay fast on DMA (the 27-point workload at 32 chunks and two
-  // rounds: 190 GCell/s), so the count queued by one run counts too.  Adjoint
-  // plans keep DMA: their reverse sweep waits for each round and its compute
-  // kernels compete with copy kernels (the 1024^3 gradient: 4.9 s with DMA,
-  // 7.2 s with copy kernels).
+  // Copy engine.  With one slot there are no copies to overlap: copy-in,
+  // launches and copy-out follow one another, and each change of engine costs
+  // an event or a wait of the host.  Copy kernels on the launches' own stream
+  // leave those out.  Measured on MI355X as a chain of copy-in, three passes
+  // and copy-out, us per chain, DMA against kernels: 16 KiB 50 and 21, 768 KiB
+  // 84 and 40, 2 MiB 130 and 87, 8 MiB 358 and 321, 64 MiB 2499 and 2453;
+  // above that the engines' 3 % higher rate outweighs the gaps.  With two or
+  // three slots the overlap has to pay for those events, which it does from
+  // about half a MiB per copy: one stream against three, runs of 2 to 8
+  // chunks, 0.15-0.3 MB 1.2 to 1.9 times faster, 0.5 MB 1.0 to 1.3, 1 MB 0.75
+  // to 1.4, 3 MB 0.6 to 0.85.  Gradients as well (0.18 MB 1.07, 0.5 MB 1.02,
+  // 1.4 MB 0.86).
+  //
+  // Otherwise DMA, whose copy-outs the host releases one by one, but copy
+  // kernels out where a run queues many copies: set when those were left to
+  // the device in one go (a 64 MiB pattern: 28-82 GB/s over repeats, kernels
+  // 84-86).  Adjoint plans keep DMA: their reverse sweep waits for each round
+  // and its compute kernels compete with copy kernels (the 1024^3 gradient:
+  // 4.9 s with DMA, 7.2 s with copy kernels).
   P->copy_engine_forced = D.copy_engine != SO2DR_COPY_AUTO;
   if (P->copy_engine_forced) {
     P->copy_engine = D.copy_engine;
+    P->serial = P->n_slots == 1;
   } else {
     int64_t own = 0;
     for (int i = 0; i < P->d; ++i) own = std::max<int64_t>(own, P->bnd[i + 1] - P->bnd[i]);
     const int64_t rounds = P->K > 0 ? (P->T + P->K - 1) / P->K : 1;
     const int64_t queued = 2 * (int64_t)P->d * rounds;
-    P->copy_engine = !P->adjoint && (size_t)own * P->plane_bytes() < kKernelCopyBelow && queued > kKernelCopyQueued
-                         ? SO2DR_COPY_KERNEL_OUT
-                         : SO2DR_COPY_DMA;
+    const size_t piece = (size_t)own * P->plane_bytes();
+    P->serial = (P->n_slots == 1 && piece <= kSerialCopyMax) || piece <= kSerialPieceMax;
+    if (P->serial && (P->n_slots == 1 || queued <= kKernelCopyQueued))
+      P->copy_engine = SO2DR_COPY_KERNEL;
+    else
+      P->copy_engine = !P->adjoint && piece < kKernelCopyBelow && queued > kKernelCopyQueued
+                           ? SO2DR_COPY_KERNEL_OUT
+                           : SO2DR_COPY_DMA;
   }
   return SO2DR_OK;
 }

@@ -42,6 +42,9 @@
 // otherwise keeps copy-outs on the copy-in's engine (a two-chunk, two-round
 // run of 20 MiB copies: 2.42 ms, but 2.91 after 45 other runs; with the empty
 // kernel 2.46 always, and the 64 MiB chunks above 186 against 185 ms).
+// Plans marked serial by the planner (one slot, or pieces so small that the
+// events cost more than the overlap gives) run in list order on streams[0]
+// alone, their host copies as copy kernels through the host mapping.
 // Nothing synchronises the device between rounds.
 #include <algorithm>
 #include <chrono>
@@ -110,7 +113,7 @@ int check_pinned(const void *p, size_t bytes, const char *what) {
   return SO2DR_OK;
 }
 
-char *mapped_host(const void *p, size_t bytes) {
+char *mapped_host(const void *p, size_t bytes, bool coherent) {
   if (!p || bytes == 0) return nullptr;
   hipPointerAttribute_t a;
   std::memset(&a, 0, sizeof(a));
@@ -118,6 +121,7 @@ char *mapped_host(const void *p, size_t bytes) {
     (void)hipGetLastError();
     return nullptr;
   }
+  if (coherent && (a.allocationFlags & hipHostMallocNonCoherent)) return nullptr;
   void *base = nullptr;
   size_t size = 0;
   if (hipMemGetAddressRange(&base, &size, a.devicePointer) != hipSuccess || !base) {
@@ -130,39 +134,30 @@ char *mapped_host(const void *p, size_t bytes) {
   return static_cast<char *>(a.devicePointer);
 }
 
-static bool kernel_copyable(const void *x, const void *y, size_t n) {
-  return (((uintptr_t)x | (uintptr_t)y | (uintptr_t)n) & 15) == 0;
+// One copy by a kernel through the host mapping.
+static int map_copy(const Plan &P, void *dst, const void *src, size_t n, bool to_host, hipStream_t s) {
+  if (launch_host_copy(dst, src, n, to_host, P.serial ? kSerialCopyWgs : kHostCopyWgs, s) == 0) return SO2DR_OK;
+  set_error("host copy kernel launch failed");
+  return SO2DR_E_HIP;
 }
 
-int copy_to_device(void *dst, const void *src_host, size_t n, const void *host_base, char *dev_base,
+int copy_to_device(const Plan &P, void *dst, const void *src_host, size_t n, const void *host_base, char *dev_base,
                    hipStream_t s) {
   if (n == 0) return SO2DR_OK;
   if (dev_base) {
     const char *src = dev_base + (static_cast<const char *>(src_host) - static_cast<const char *>(host_base));
-    if (kernel_copyable(dst, src, n)) {
-      if (launch_dcopy(dst, src, n, s, kHostCopyWgs)) {
-        set_error("host copy kernel launch failed");
-        return SO2DR_E_HIP;
-      }
-      return SO2DR_OK;
-    }
+    return map_copy(P, dst, src, n, false, s);
   }
   HIPCHK(hipMemcpyAsync(dst, src_host, n, hipMemcpyHostToDevice, s));
   return SO2DR_OK;
 }
 
-int copy_to_host(void *dst_host, const void *src, size_t n, const void *host_base, char *dev_base,
+int copy_to_host(const Plan &P, void *dst_host, const void *src, size_t n, const void *host_base, char *dev_base,
                  hipStream_t s) {
   if (n == 0) return SO2DR_OK;
   if (dev_base) {
     char *dst = dev_base + (static_cast<char *>(dst_host) - static_cast<const char *>(host_base));
-    if (kernel_copyable(dst, src, n)) {
-      if (launch_dcopy(dst, src, n, s, kHostCopyWgs)) {
-        set_error("host copy kernel launch failed");
-        return SO2DR_E_HIP;
-      }
-      return SO2DR_OK;
-    }
+    return map_copy(P, dst, src, n, true, s);
   }
   HIPCHK(hipMemcpyAsync(dst_host, src, n, hipMemcpyDeviceToHost, s));
   return SO2DR_OK;
@@ -280,8 +275,9 @@ int execute(Plan &P, const void *host_in, void *host_out, int steps, so2dr_stats
   char *dev_in = nullptr, *dev_out = nullptr;
   bool k_in = P.copy_engine == SO2DR_COPY_KERNEL;
   if (k_in || P.copy_engine == SO2DR_COPY_KERNEL_OUT) {
-    dev_in = mapped_host(host_in, field);
-    dev_out = host_out == host_in ? dev_in : mapped_host(host_out, field);
+    const bool coherent = !P.copy_engine_forced;
+    dev_in = mapped_host(host_in, field, coherent);
+    dev_out = host_out == host_in ? dev_in : mapped_host(host_out, field, coherent);
     if (!dev_in || !dev_out) {
       if (P.copy_engine_forced) {
         set_error("copy kernels need each host array inside one page-locked allocation mapped into the device");
@@ -301,7 +297,8 @@ int execute(Plan &P, const void *host_in, void *host_out, int steps, so2dr_stats
   }
   int64_t computed = 0;
   const std::vector<so2dr_op> ops = build_ops(P, steps, &computed);
-  const int ns = (int)P.streams.size();
+  // serial plans: with copy kernels the whole run is one stream's, in list order
+  const int ns = P.serial && dev_out ? 1 : (int)P.streams.size();
   std::vector<int> strm;
   std::vector<int64_t> waits;
   schedule_deps(P, ops, ns, &strm, &waits);
@@ -351,7 +348,7 @@ int execute(Plan &P, const void *host_in, void *host_out, int steps, so2dr_stats
         const char *base = op.round == 0 ? hin : hout;
         char *dev = !k_in ? nullptr : op.round == 0 ? dev_in : dev_out;
         char *dst = P.slot_buf(op.slot, op.buf_out) + (size_t)(op.z0 - op.buf_z0) * pb;
-        rc = copy_to_device(dst, base + (size_t)op.z0 * pb, (size_t)(op.z1 - op.z0) * pb, base, dev, s);
+        rc = copy_to_device(P, dst, base + (size_t)op.z0 * pb, (size_t)(op.z1 - op.z0) * pb, base, dev, s);
         if (rc) return rc;
         S.bytes_h2d += (uint64_t)(op.z1 - op.z0) * pb;
         break;
@@ -422,7 +419,7 @@ int execute(Plan &P, const void *host_in, void *host_out, int steps, so2dr_stats
       }
       case SO2DR_OP_D2H: {
         const char *src = P.slot_buf(op.slot, op.buf_in) + (size_t)(op.z0 - op.buf_z0) * pb;
-        rc = copy_to_host(hout + (size_t)op.z0 * pb, src, (size_t)(op.z1 - op.z0) * pb, hout, dev_out, s);
+        rc = copy_to_host(P, hout + (size_t)op.z0 * pb, src, (size_t)(op.z1 - op.z0) * pb, hout, dev_out, s);
         if (rc) return rc;
         S.bytes_d2h += (uint64_t)(op.z1 - op.z0) * pb;
         if (op.chunk == P.d - 1) S.rounds_done = op.round + 1;

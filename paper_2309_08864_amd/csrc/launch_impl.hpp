@@ -8,6 +8,7 @@
 #include "lane_tile.hpp"
 #include "launch.hpp"
 #include "march2d_kernel.hpp"
+#include "wide2d_kernel.hpp"
 #include "march_kernel.hpp"
 #include "tb_kernel.hpp"
 
@@ -222,11 +223,12 @@ struct March3d {
   }
 };
 
-template <typename T, bool BOX, int R, int KL, int VX, int PF, bool ROT, bool RAS = false>
-int launch_march2d_one(const LaunchParams &p, hipStream_t stream, std::string *msg) {
-  using A = typename Store<T>::A;
-  using G = RowTile<R, KL, VX>;
-  using S = Stencil<2, BOX, R>;
+// One launch of a 2D kernel over row tiles G: `rows` input rows per step (a
+// segment ends with a step where it can), `extra` rows' work besides its own
+// per segment, `issue` and `lat` cycles per row as in plan_march.
+template <typename S, typename G, typename A>
+int launch_rows(void (*kernel)(TbArgs<A>), const LaunchParams &p, int rows, int halo, int extra, double lat, double issue,
+                std::atomic<int> *per_cu, hipStream_t stream, std::string *msg) {
   if (p.npts != S::npts()) {
     if (msg) *msg = "weight count does not match the stencil";
     return -1;
@@ -234,18 +236,12 @@ int launch_march2d_one(const LaunchParams &p, hipStream_t stream, std::string *m
   TbArgs<A> a = launch_args<A>(p, S::npts());
   a.ntx = (int)((p.nx + G::OX - 1) / G::OX);
   a.nty = 1;
-  const auto kernel = march2d_kernel<T, BOX, R, KL, VX, PF, ROT, RAS>;
-  static std::atomic<int> per_cu{-1};
-  const int64_t slots = resident_wgs((const void *)kernel, 64 * kRowWaves, &per_cu);
-  const int occ = std::max(1, per_cu.load(std::memory_order_relaxed));
-  // a wave's instructions per row (as for the 3D shapes) at 4 cycles each; the
-  // latency from launches of 2, 3 and 4 waves per SIMD (12800 x 3260, two
-  // levels of the radius-2 box: 93, 87, 86 us)
-  constexpr double issue = 4.0 * (KL * (VX * S::npts() + 4.0) + 10.0), lat = 900.0;
-  const MarchPlan mp = plan_march(p.out_hi - p.out_lo, a.ntx, 2 * KL * R + KL - 1, slots > 0 ? (int)(slots / occ) : 256,
-                                  occ, lat, issue, kRowWaves);
-  a.zseg = mp.zseg;
-  a.nseg = mp.nseg;
+  const int64_t slots = resident_wgs((const void *)kernel, 64 * kRowWaves, per_cu);
+  const int occ = std::max(1, per_cu->load(std::memory_order_relaxed));
+  const int64_t span = p.out_hi - p.out_lo;
+  const MarchPlan mp = plan_march(span, a.ntx, extra, slots > 0 ? (int)(slots / occ) : 256, occ, lat, issue, kRowWaves);
+  a.zseg = (mp.zseg + halo + rows - 1) / rows * rows - halo;
+  a.nseg = (int)((span + a.zseg - 1) / a.zseg);
   const int64_t nwg = ((int64_t)a.ntx * a.nseg + kRowWaves - 1) / kRowWaves;
   if (nwg > 0x7fffffff / kRowWaves) {
     if (msg) *msg = "grid too large for one launch";
@@ -258,6 +254,29 @@ int launch_march2d_one(const LaunchParams &p, hipStream_t stream, std::string *m
     return -5;
   }
   return 0;
+}
+
+template <typename T, bool BOX, int R, int KL, int VX, int PF, bool ROT, bool RAS = false>
+int launch_march2d_one(const LaunchParams &p, hipStream_t stream, std::string *msg) {
+  using S = Stencil<2, BOX, R>;
+  // a wave's instructions per row (as for the 3D shapes) at 4 cycles each; the
+  // latency from launches of 2, 3 and 4 waves per SIMD (12800 x 3260, two
+  // levels of the radius-2 box: 93, 87, 86 us)
+  constexpr double issue = 4.0 * (KL * (VX * S::npts() + 4.0) + 10.0), lat = 900.0;
+  static std::atomic<int> per_cu{-1};
+  return launch_rows<S, RowTile<R, KL, VX>>(march2d_kernel<T, BOX, R, KL, VX, PF, ROT, RAS>, p, 1, 2 * KL * R,
+                                            2 * KL * R + KL - 1, lat, issue, &per_cu, stream, msg);
+}
+
+template <typename T, int R, int VX, int U>
+int launch_wide2d_one(const LaunchParams &p, hipStream_t stream, std::string *msg) {
+  using S = Stencil<2, true, R>;
+  // a segment's two ends cost about two rows: the rows of weights that none of
+  // its outputs needs are skipped.  A latency of 1800 cycles per step chose
+  // within 2 % of the best of 300 to 3000 on six grids (400 x 400 to 12800^2).
+  constexpr double issue = 4.0 * (VX * S::npts() + 30.0), lat = 1800.0 / U;
+  static std::atomic<int> per_cu{-1};
+  return launch_rows<S, RowTile<R, 1, VX>>(wide2d_kernel<T, R, VX, U>, p, U, 2 * R, 2, lat, issue, &per_cu, stream, msg);
 }
 
 // Bytes of the march kernel's halo buffers.
@@ -304,14 +323,20 @@ int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
   if constexpr (NDIM == 2) {
     // Unrolling by the stencil width is kept while the unrolled body stays
     // within 3000 FMAs (12 KiB of code; 2400 in FP64, whose FMAs take twice the
-    // code): one level of the radius-4 box, 2916
-    // of them, takes 464 us on 12800^2 unrolled and 489 us with shifting sums.
+    // code): in this kernel one level of the radius-4 box, 2916 of them, took
+    // 464 us on 12800^2 unrolled and 489 us with shifting sums.
     // FP64 lanes own two cells: four need 158 registers at 4 levels, three
     // waves per SIMD, and 93 us on 4800^2 where two need 82; two levels of the
-    // radius-3 box gain 10 %.
+    // radius-3 box gain 10 %.  One level of a box of radius 3 or 4 has a kernel
+    // of its own, which is faster at every size (its header has the figures).
     constexpr int VX = sizeof(T) == 8 ? 2 : 4;
     constexpr bool rot = (int64_t)KL * VX * Stencil<2, BOX, R>::npts() * (2 * R + 1) > (sizeof(T) == 8 ? 2400 : 3000);
-    if (march_fits<T, 1>(p)) return launch_march2d_one<T, BOX, R, KL, VX, 2, rot, RAS>(p, s, msg);
+    if (march_fits<T, 1>(p)) {
+      if constexpr (BOX && R >= 3 && KL == 1)
+        return launch_wide2d_one<T, R, VX, 4>(p, s, msg);
+      else
+        return launch_march2d_one<T, BOX, R, KL, VX, 2, rot, RAS>(p, s, msg);
+    }
   }
   if constexpr (NDIM == 3) {
     constexpr bool single = KL == 1 && march_lds<A, KL, 16, R, 4, 2>() <= kLdsMax;

@@ -377,9 +377,9 @@ int make_plan(const so2dr_desc &D, Plan *P) {
     // the fused depth whose launches update cells fastest as measured on
     // MI355X for this stencil and storage type (rates.hpp): e.g. FP32 3 for
     // the 7-point star, 2 for the 13-point star and the 27-point box, 7 for
-    // the 2D 5-point star, 1 for the widest boxes (bound by arithmetic:
-    // fusing only adds tile-edge recomputation)
-    const int pref = preferred_depth(P->dtype, P->stencil, P->max_k_on);
+    // the 2D 5-point star, 1 for the radius-4 box (bound by arithmetic: fusing
+    // only adds tile-edge recomputation)
+    const int pref = preferred_depth(P->dtype, P->stencil, P->max_k_on, (uint64_t)P->N * P->plane_bytes());
     P->k_on = std::max(1, std::min(pref, P->K));
   }
   P->budget = D.device_budget_bytes;

@@ -8,6 +8,7 @@
 // output rows of 38400 cells in 2D.  The 2D chunks of 16-bit storage fit
 // the 256 MiB last-level cache in part, which their rates include.
 #pragma once
+#include <stdint.h>
 
 namespace so2dr {
 
@@ -18,8 +19,8 @@ constexpr double kRate[4][8][8] = {
         {624, 1178, 1688, 2251, 2725, 3121, 3255, 3359},  // 2D star r1
         {621, 1171, 1738, 2038, 2094, 2284, 2331, 2396},  // 2D box r1
         {604, 860, 890, 972, 0, 0, 0, 0},                 // 2D box r2
-        {474, 485, 482, 473, 0, 0, 0, 0},                 // 2D box r3
-        {293, 271, 275, 256, 0, 0, 0, 0},                 // 2D box r4
+        {473, 478, 481, 473, 0, 0, 0, 0},                 // 2D box r3
+        {315, 269, 275, 257, 0, 0, 0, 0},                 // 2D box r4
         {546, 1148, 1519, 1301, 0, 0, 0, 0},              // 3D star r1
         {556, 917, 0, 0, 0, 0, 0, 0},                     // 3D star r2
         {548, 771, 679, 530, 0, 0, 0, 0},                 // 3D box r1
@@ -29,8 +30,8 @@ constexpr double kRate[4][8][8] = {
         {299, 574, 852, 1170, 0, 0, 0, 0},
         {296, 570, 859, 1171, 0, 0, 0, 0},
         {286, 580, 0, 0, 0, 0, 0, 0},
-        {268, 319, 0, 0, 0, 0, 0, 0},
-        {167, 166, 0, 0, 0, 0, 0, 0},
+        {292, 319, 0, 0, 0, 0, 0, 0},
+        {237, 168, 0, 0, 0, 0, 0, 0},
         {280, 517, 0, 0, 0, 0, 0, 0},
         {260, 446, 0, 0, 0, 0, 0, 0},
         {270, 511, 0, 0, 0, 0, 0, 0},
@@ -40,8 +41,8 @@ constexpr double kRate[4][8][8] = {
         {1504, 2724, 3144, 3129, 3041, 3103, 3068, 3084},
         {1453, 2261, 2306, 2362, 2268, 2252, 2244, 2232},
         {911, 971, 976, 999, 0, 0, 0, 0},
-        {525, 544, 495, 461, 0, 0, 0, 0},
-        {293, 284, 262, 255, 0, 0, 0, 0},
+        {526, 549, 496, 463, 0, 0, 0, 0},
+        {349, 284, 263, 255, 0, 0, 0, 0},
         {1002, 1490, 1545, 1241, 0, 0, 0, 0},
         {769, 913, 0, 0, 0, 0, 0, 0},
         {622, 818, 756, 516, 0, 0, 0, 0},
@@ -51,8 +52,8 @@ constexpr double kRate[4][8][8] = {
         {1482, 2746, 2934, 2923, 3033, 3075, 3003, 2982},
         {1462, 2154, 2232, 2280, 2177, 2234, 2265, 2244},
         {898, 958, 991, 995, 0, 0, 0, 0},
-        {504, 534, 494, 457, 0, 0, 0, 0},
-        {306, 289, 268, 260, 0, 0, 0, 0},
+        {519, 535, 495, 458, 0, 0, 0, 0},
+        {347, 288, 268, 260, 0, 0, 0, 0},
         {992, 1365, 1445, 1164, 0, 0, 0, 0},
         {746, 886, 0, 0, 0, 0, 0, 0},
         {619, 788, 742, 511, 0, 0, 0, 0},
@@ -74,21 +75,24 @@ constexpr double kernel_rate(int dtype, int stencil, int levels) {
 // level on MI355X, (1201 x 1003, 12800 x 3360, 12800 x 12800):
 //   FP32 2D 9-point box   5 levels 2.4 18.2 61.2, 6: 2.4 17.8 57.4, 8: 2.5 18.6 58.7
 //   FP32 2D 25-point box  2 levels 4.5 43.4 147,  3: 4.6 42.0 139,  4: 4.9 42.4 139
+//   FP32 2D 49-point box  1 level  8.0 87 296,    2: 8.4 78 261
 //   FP32 2D 5-point star  6 levels 2.0 13.1 47.8, 7: 2.1 12.7 43.3, 8: 2.1 12.4 40.8
-//   FP64 2D 49-point box  1 level  18.5 171 596,  2: 14.6 123 424
+//   FP64 2D 49-point box  1 level  10.5 151 561,  2: 14.7 116 405 (4800 x 4800:
+//     83 and 93): one level in fields up to the last-level cache's 256 MiB
 // and for 251 x 190 x 163 and 640 x 512 x 256
 //   FP64 3D 13-point star 1 level  29.3 288,      2: 20.1 198
 // 16-bit storage: a round-at-store run rounds once per launch, so that its
 // values depend on the depth, which is part of the plan's result and stays
 // where it is (each is within 12 % of the best rate above).
 constexpr int kDepth[4][8] = {
-    {7, 6, 3, 1, 1, 3, 2, 2},
+    {7, 6, 3, 2, 1, 3, 2, 2},
     {4, 4, 2, 2, 1, 2, 2, 2},
     {3, 3, 2, 1, 1, 3, 2, 2},
     {3, 3, 2, 1, 1, 3, 2, 2},
 };
-constexpr int preferred_depth(int dtype, int stencil, int max_depth) {
-  const int d = (dtype >= 0 && dtype < 4 && stencil >= 0 && stencil < 8) ? kDepth[dtype][stencil] : 1;
+constexpr int preferred_depth(int dtype, int stencil, int max_depth, uint64_t field_bytes) {
+  int d = (dtype >= 0 && dtype < 4 && stencil >= 0 && stencil < 8) ? kDepth[dtype][stencil] : 1;
+  if (dtype == 1 && stencil == 3 && field_bytes <= (uint64_t)256 << 20) d = 1;
   return d < max_depth ? d : max_depth;
 }
 

@@ -223,12 +223,25 @@ struct March3d {
   }
 };
 
-// One launch of a 2D kernel over row tiles G: `rows` input rows per step (a
-// segment ends with a step where it can), `extra` rows' work besides its own
-// per segment, `issue` and `lat` cycles per row as in plan_march.
+// Segmenting of one launch of a 2D kernel over row tiles G: `rows` input rows
+// per step (a segment ends with a step where it can), `extra` rows' work besides
+// its own per segment, `issue` and `lat` cycles per row as in plan_march.
+template <typename G, typename A>
+MarchPlan plan_rows(void (*kernel)(TbArgs<A>), const LaunchParams &p, int rows, int halo, int extra, double lat,
+                    double issue, std::atomic<int> *per_cu) {
+  const int64_t slots = resident_wgs((const void *)kernel, 64 * kRowWaves, per_cu);
+  const int occ = std::max(1, per_cu->load(std::memory_order_relaxed));
+  const int64_t span = p.out_hi - p.out_lo;
+  MarchPlan mp = plan_march(span, (p.nx + G::OX - 1) / G::OX, extra, slots > 0 ? (int)(slots / occ) : 256, occ, lat,
+                            issue, kRowWaves);
+  mp.zseg = (mp.zseg + halo + rows - 1) / rows * rows - halo;
+  mp.nseg = (int)((span + mp.zseg - 1) / mp.zseg);
+  return mp;
+}
+
 template <typename S, typename G, typename A>
-int launch_rows(void (*kernel)(TbArgs<A>), const LaunchParams &p, int rows, int halo, int extra, double lat, double issue,
-                std::atomic<int> *per_cu, hipStream_t stream, std::string *msg) {
+int launch_rows(void (*kernel)(TbArgs<A>), const LaunchParams &p, const MarchPlan &mp, hipStream_t stream,
+                std::string *msg) {
   if (p.npts != S::npts()) {
     if (msg) *msg = "weight count does not match the stencil";
     return -1;
@@ -236,12 +249,8 @@ int launch_rows(void (*kernel)(TbArgs<A>), const LaunchParams &p, int rows, int 
   TbArgs<A> a = launch_args<A>(p, S::npts());
   a.ntx = (int)((p.nx + G::OX - 1) / G::OX);
   a.nty = 1;
-  const int64_t slots = resident_wgs((const void *)kernel, 64 * kRowWaves, per_cu);
-  const int occ = std::max(1, per_cu->load(std::memory_order_relaxed));
-  const int64_t span = p.out_hi - p.out_lo;
-  const MarchPlan mp = plan_march(span, a.ntx, extra, slots > 0 ? (int)(slots / occ) : 256, occ, lat, issue, kRowWaves);
-  a.zseg = (mp.zseg + halo + rows - 1) / rows * rows - halo;
-  a.nseg = (int)((span + a.zseg - 1) / a.zseg);
+  a.zseg = mp.zseg;
+  a.nseg = mp.nseg;
   const int64_t nwg = ((int64_t)a.ntx * a.nseg + kRowWaves - 1) / kRowWaves;
   if (nwg > 0x7fffffff / kRowWaves) {
     if (msg) *msg = "grid too large for one launch";
@@ -256,28 +265,45 @@ int launch_rows(void (*kernel)(TbArgs<A>), const LaunchParams &p, int rows, int 
   return 0;
 }
 
+// One shape of march2d_kernel: its segmenting and predicted cost, and the launch.
 template <typename T, bool BOX, int R, int KL, int VX, int PF, bool ROT, bool RAS = false>
-int launch_march2d_one(const LaunchParams &p, hipStream_t stream, std::string *msg) {
+struct March2d {
+  using G = RowTile<R, KL, VX>;
   using S = Stencil<2, BOX, R>;
-  // a wave's instructions per row (as for the 3D shapes) at 4 cycles each; the
-  // latency from launches of 2, 3 and 4 waves per SIMD (12800 x 3260, two
-  // levels of the radius-2 box: 93, 87, 86 us)
-  constexpr double issue = 4.0 * (KL * (VX * S::npts() + 4.0) + 10.0), lat = 900.0;
-  static std::atomic<int> per_cu{-1};
-  return launch_rows<S, RowTile<R, KL, VX>>(march2d_kernel<T, BOX, R, KL, VX, PF, ROT, RAS>, p, 1, 2 * KL * R,
-                                            2 * KL * R + KL - 1, lat, issue, &per_cu, stream, msg);
-}
+  static constexpr auto kernel = march2d_kernel<T, BOX, R, KL, VX, PF, ROT, RAS>;
 
+  static MarchPlan plan(const LaunchParams &p) {
+    // a wave's instructions per row (as for the 3D shapes) at 4 cycles each; the
+    // latency from launches of 2, 3 and 4 waves per SIMD (12800 x 3260, two
+    // levels of the radius-2 box: 93, 87, 86 us)
+    constexpr double issue = 4.0 * (KL * (VX * S::npts() + 4.0) + 10.0), lat = 900.0;
+    static std::atomic<int> per_cu{-1};
+    return plan_rows<G>(kernel, p, 1, 2 * KL * R, 2 * KL * R + KL - 1, lat, issue, &per_cu);
+  }
+  static int launch(const LaunchParams &p, const MarchPlan &mp, hipStream_t stream, std::string *msg) {
+    return launch_rows<S, G>(kernel, p, mp, stream, msg);
+  }
+};
+
+// One shape of wide2d_kernel: its segmenting and predicted cost, and the launch.
 template <typename T, int R, int VX, int U>
-int launch_wide2d_one(const LaunchParams &p, hipStream_t stream, std::string *msg) {
+struct Wide2d {
+  using G = RowTile<R, 1, VX>;
   using S = Stencil<2, true, R>;
-  // a segment's two ends cost about two rows: the rows of weights that none of
-  // its outputs needs are skipped.  A latency of 1800 cycles per step chose
-  // within 2 % of the best of 300 to 3000 on six grids (400 x 400 to 12800^2).
-  constexpr double issue = 4.0 * (VX * S::npts() + 30.0), lat = 1800.0 / U;
-  static std::atomic<int> per_cu{-1};
-  return launch_rows<S, RowTile<R, 1, VX>>(wide2d_kernel<T, R, VX, U>, p, U, 2 * R, 2, lat, issue, &per_cu, stream, msg);
-}
+  static constexpr auto kernel = wide2d_kernel<T, R, VX, U>;
+
+  static MarchPlan plan(const LaunchParams &p) {
+    // a segment's two ends cost about two rows: the rows of weights that none of
+    // its outputs needs are skipped.  A latency of 1800 cycles per step chose
+    // within 2 % of the best of 300 to 3000 on six grids (400 x 400 to 12800^2).
+    constexpr double issue = 4.0 * (VX * S::npts() + 30.0), lat = 1800.0 / U;
+    static std::atomic<int> per_cu{-1};
+    return plan_rows<G>(kernel, p, U, 2 * R, 2, lat, issue, &per_cu);
+  }
+  static int launch(const LaunchParams &p, const MarchPlan &mp, hipStream_t stream, std::string *msg) {
+    return launch_rows<S, G>(kernel, p, mp, stream, msg);
+  }
+};
 
 // Bytes of the march kernel's halo buffers.
 template <typename A, int KL, int NW, int R, int VX, int HB>
@@ -329,13 +355,31 @@ int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
     // waves per SIMD, and 93 us on 4800^2 where two need 82; two levels of the
     // radius-3 box gain 10 %.  One level of a box of radius 3 or 4 has a kernel
     // of its own, which is faster at every size (its header has the figures).
+    // Grids that do not fill the chip take two cells per lane in FP32 and 16
+    // bits as well, where the cost model says so: a wave's rows end sooner and
+    // twice the tiles cover them.  us per launch on 400 x 400 (and 1201 x 1003),
+    // two cells against four: 7 levels of the 5-point star 9.9 (14.7) and 11.6
+    // (14.7), 6 of the radius-1 box 8.9 (13.9) and 10.7 (14.3), 3 of the radius-2
+    // box 7.9 (12.9) and 10.3 (13.9), 2 of the radius-3 box 8.5 (14.2) and 11.8
+    // (16.2), one of the radius-4 box 6.6 (11.3) and 9.1 (12.1).
     constexpr int VX = sizeof(T) == 8 ? 2 : 4;
-    constexpr bool rot = (int64_t)KL * VX * Stencil<2, BOX, R>::npts() * (2 * R + 1) > (sizeof(T) == 8 ? 2400 : 3000);
+    constexpr bool wide = BOX && R >= 3 && KL == 1;
     if (march_fits<T, 1>(p)) {
-      if constexpr (BOX && R >= 3 && KL == 1)
-        return launch_wide2d_one<T, R, VX, 4>(p, s, msg);
-      else
-        return launch_march2d_one<T, BOX, R, KL, VX, 2, rot, RAS>(p, s, msg);
+      auto shape = [&](auto vx) {
+        constexpr int V = decltype(vx)::value;
+        constexpr bool rot = (int64_t)KL * V * Stencil<2, BOX, R>::npts() * (2 * R + 1) > (sizeof(T) == 8 ? 2400 : 3000);
+        using M = March2d<T, BOX, R, KL, V, 2, rot, RAS>;
+        using W = Wide2d<T, R, V, 4>;
+        return typename std::conditional<wide, W, M>::type{};
+      };
+      using Full = decltype(shape(std::integral_constant<int, VX>{}));
+      const MarchPlan f = Full::plan(p);
+      if constexpr (VX == 4) {
+        using Half = decltype(shape(std::integral_constant<int, 2>{}));
+        const MarchPlan h = Half::plan(p);
+        if (h.cost < f.cost) return Half::launch(p, h, s, msg);
+      }
+      return Full::launch(p, f, s, msg);
     }
   }
   if constexpr (NDIM == 3) {
@@ -358,6 +402,11 @@ int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
     constexpr int NWW = single ? 16 : 8, MW = single ? 2 : tall ? 6 : 4;
     constexpr int HBW = single || square || tall ? 2 : HB, HAW = single || square ? HA4 : VXW;
     using Narrow = March3d<T, BOX, R, KL, 8, 4, 1, 2, 2, 1, RAS>;
+    // half the waves and rows: a grid that does not fill the chip ends its march
+    // steps sooner, and more tiles cover it (us, small against narrow: 3 levels
+    // of the 7-point star on 48x40x30 5.7 and 7.3, 80x84x49 7.6 and 8.8; 2 of the
+    // 13-point star 6.8 and 9.0, 9.2 and 11.1; 2 of the 27-point box 5.5 and 7.4)
+    using Small = March3d<T, BOX, R, KL, 4, 4, 1, 2, 2, 1, RAS>;
     // two levels whose halo takes a quarter of 32 rows or whose box costs most
     // have a taller narrow shape, 8 waves of 6 rows: BF16 13-point on
     // 301x257x203 52 us against 57, 27-point 59 against 62
@@ -370,6 +419,8 @@ int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
           const MarchPlan n6 = Narrow6::plan(p);
           if (n6.cost < n.cost) return Narrow6::launch(p, n6, s, msg);
         }
+        const MarchPlan q = Small::plan(p);
+        if (q.cost < n.cost) return Small::launch(p, q, s, msg);
         return Narrow::launch(p, n, s, msg);
       };
       const uint64_t moved = (uint64_t)(std::min(p.in_hi, p.n_axis) - std::max<int64_t>(p.in_lo, 0) + p.out_hi - p.out_lo) *
@@ -380,7 +431,7 @@ int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
         if (march_fits<T, VXW>(p)) {
           const MarchPlan w = Wide::plan(p);
           if (streams) return Wide::launch(p, w, s, msg);
-          double best = Narrow::plan(p).cost;
+          double best = std::min(Narrow::plan(p).cost, Small::plan(p).cost);
           if constexpr (two_narrow) best = std::min(best, Narrow6::plan(p).cost);
           return w.cost < 0.8 * best ? Wide::launch(p, w, s, msg) : narrow();
         }

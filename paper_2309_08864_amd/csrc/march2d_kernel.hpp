@@ -36,18 +36,11 @@
 // area, which are never stored, depend on them.
 #pragma once
 #include "march_kernel.hpp"
+#include "row_tile.hpp"
 
 namespace so2dr {
 
 constexpr int kRowWaves = 4;  // one per SIMD of a CU
-
-template <int R, int KL, int VX>
-struct RowTile {
-  static constexpr int TX = 64 * VX;
-  static constexpr int HX = (KL * R + VX - 1) / VX * VX;
-  static constexpr int OX = TX - 2 * HX;
-  static_assert(R <= 2 * VX && OX > 0, "tile too small for this depth");
-};
 
 enum { kInside = 0, kEdge = 1, kEdgeCells = 2 };
 
@@ -75,12 +68,8 @@ __device__ __forceinline__ void march2d_tile(const TbArgs<typename Store<T>::A> 
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     const int gx = gx0 + j;
-    int lx = gx;
-    keep[j] = true;
-    if (EDGE && (gx < 0 || gx >= a.nx)) {
-      if (a.per_x) lx = ((gx % a.nx) + a.nx) % a.nx; else { lx = 0; keep[j] = false; }
-    }
-    boff[j] = (uint32_t)lx * (uint32_t)sizeof(T);
+    keep[j] = !EDGE || (gx >= 0 && gx < a.nx) || a.per_x;
+    boff[j] = (uint32_t)(EDGE ? row_source(gx, a.nx, VX / NV, a.per_x) : gx) * (uint32_t)sizeof(T);
     st[j] = cx0 >= G::HX && cx0 < G::TX - G::HX && (!EDGE || gx < a.nx);
   }
 
@@ -204,13 +193,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void march2d_kernel(const TbArgs<ty
   const int zo0 = (int)a.out_lo + seg * (int)a.zseg;
   if (zo0 >= (int)a.out_hi) return;
   const int zo1 = min(zo0 + (int)a.zseg, (int)a.out_hi);
-  int x_lo = tx_i * G::OX - G::HX;
-  const int over = a.nx % VX;   // cells of the row's last, partial vector
-  bool cells = false;
-  if (over != 0 && x_lo + G::TX > a.nx) {
-    cells = x_lo < VX;
-    if (!cells) x_lo -= VX - over;
-  }
+  const auto [x_lo, cells] = row_start<G, VX>(tx_i, a.nx);
   const int P0 = zo0 - KL * R, n_load = zo1 - zo0 + 2 * KL * R;
   const bool edge = x_lo < 0 || x_lo + G::TX > a.nx || P0 - 2 * R < 0 || P0 + n_load + R > (int)a.n_axis;
   if (!edge)

@@ -293,12 +293,17 @@ static size_t plan_bytes(Plan &P, int d, int slots, bool lean = false, int64_t b
 // of the chip idle and costs a launch and its latency (2D 5-point star in
 // FP64, 1024 x 1024 in four chunks under 4 MiB, 16 steps: 3.40 ms at 16
 // planes, 2.23 ms at 132).  Taken is the least number of sub-blocks per launch
-// of the tallest chunk that fits, and the shortest block that gives it.
+// of the tallest chunk that fits, and the shortest block that gives it.  A
+// layout that so2dr_run_noalloc takes at its least stays one: it grows within
+// the static workspace.
 static void grow_lean_block(Plan &P) {
   const int d = P.d, slots = P.n_slots;
   const int64_t least = P.lean_block, rows = P.slot_planes - P.lean_extra;
+  const size_t limit = plan_bytes(P, d, slots, true) <= SO2DR_NOALLOC_MAX_BYTES
+                           ? std::min(P.budget, SO2DR_NOALLOC_MAX_BYTES)
+                           : P.budget;
   for (int64_t n = 1; (rows + n - 1) / n > least; ++n)
-    if (plan_bytes(P, d, slots, true, (rows + n - 1) / n) <= P.budget) return;
+    if (plan_bytes(P, d, slots, true, (rows + n - 1) / n) <= limit) return;
   plan_bytes(P, d, slots, true);
 }
 

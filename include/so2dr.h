@@ -341,8 +341,10 @@ int so2dr_plan_predict(const struct so2dr_plan *plan, const so2dr_machine *m, in
  * weights pointer is copied, not the weights).  K is taken from a geometric
  * set up to T, d up to 32 and to the 2rK-planes-per-chunk limit; a
  * candidate replaces a cheaper-looking earlier one (fewer chunks, levels or
- * shallower rounds) only when predicted more than 1 % faster.  *ms (may be
- * NULL) receives the predicted time.  Returns SO2DR_OK, the descriptor's
+ * shallower rounds) only when predicted more than 1 % faster.  The depths are
+ * part of a SO2DR_ROUND_AT_STORE plan's values, so such plans are ranked by
+ * figures that do not follow the kernels' speed.  *ms (may be NULL) receives
+ * the time predicted for the plan found.  Returns SO2DR_OK, the descriptor's
  * validation error, or E_BUDGET when no candidate fits. */
 int so2dr_plan_suggest(const so2dr_desc *desc, const so2dr_machine *m, so2dr_desc *out,
                        double *ms);

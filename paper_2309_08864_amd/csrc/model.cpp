@@ -148,6 +148,12 @@ int suggest(const so2dr_desc &in, const so2dr_machine *mp, so2dr_desc *out, doub
   if (rc) return rc;
   so2dr_machine m;
   if (mp) m = *mp; else default_machine(base, &m);
+  // Round-at-store plans are ranked by the figures, block heights and copy
+  // engines they were first ranked by, whatever has become faster since: their
+  // depths decide how often a run rounds.
+  so2dr_machine rank = m;
+  if (base.ras && !mp)
+    for (int k = 0; k < 8; ++k) rank.gupd[k] = m.gupd[k] > 0 ? kRateAtStore[base.dtype - SO2DR_BF16][base.stencil][k] : 0.0;
   const int T = in.T;
   const std::vector<int> Ks = in.tb_depth > 0 ? std::vector<int>{std::min(in.tb_depth, std::max(T, 1))}
                                               : depth_candidates(std::max(T, 1));
@@ -178,7 +184,8 @@ int suggest(const so2dr_desc &in, const so2dr_machine *mp, so2dr_desc *out, doub
         c.k_on = kon;
         Plan P;
         if (make_plan(c, &P) != SO2DR_OK) continue;
-        const double t = predict_seconds(P, m, T);
+        if (P.ras) at_store_ranking(P);
+        const double t = predict_seconds(P, rank, T);
         if (best < 0 || t < best * (1 - kMinGain)) {
           best = t;
           best_d = c;
@@ -192,6 +199,12 @@ int suggest(const so2dr_desc &in, const so2dr_machine *mp, so2dr_desc *out, doub
     return SO2DR_E_BUDGET;
   }
   *out = best_d;
+  if (base.ras) {
+    Plan P;
+    rc = make_plan(best_d, &P);
+    if (rc) return rc;
+    best = predict_seconds(P, m, T);
+  }
   if (pred_ms) *pred_ms = 1e3 * best;
   set_error("");
   return SO2DR_OK;

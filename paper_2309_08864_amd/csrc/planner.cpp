@@ -307,6 +307,28 @@ static void grow_lean_block(Plan &P) {
   plan_bytes(P, d, slots, true);
 }
 
+// Bytes of the largest chunk's copy, and the host copies a run of T steps queues.
+static size_t copy_piece(const Plan &P) {
+  int64_t own = 0;
+  for (int i = 0; i < P.d; ++i) own = std::max<int64_t>(own, P.bnd[i + 1] - P.bnd[i]);
+  return (size_t)own * P.plane_bytes();
+}
+static int64_t copies_queued(const Plan &P) { return 2 * (int64_t)P.d * (P.K > 0 ? (P.T + P.K - 1) / P.K : 1); }
+static bool kernel_out_pays(const Plan &P) {
+  return !P.adjoint && copy_piece(P) < kKernelCopyBelow && copies_queued(P) > kKernelCopyQueued;
+}
+
+// The parts of a plan that the search for round-at-store plans goes by: the
+// least sub-blocks, and copies by the engines, copy kernels out where more than
+// kKernelCopyQueued are queued.
+void at_store_ranking(Plan &P) {
+  if (P.lean) plan_bytes(P, P.d, P.n_slots, true);
+  if (!P.copy_engine_forced) {
+    P.serial = false;
+    P.copy_engine = kernel_out_pays(P) ? SO2DR_COPY_KERNEL_OUT : SO2DR_COPY_DMA;
+  }
+}
+
 static bool chunks_ok(const Plan &P, int d) {
   // every chunk but the last hands its top 2 r K planes to the next one, so
   // it must own at least that many (paper: halo space <= chunk)
@@ -483,18 +505,12 @@ int make_plan(const so2dr_desc &D, Plan *P) {
     P->copy_engine = D.copy_engine;
     P->serial = P->n_slots == 1;
   } else {
-    int64_t own = 0;
-    for (int i = 0; i < P->d; ++i) own = std::max<int64_t>(own, P->bnd[i + 1] - P->bnd[i]);
-    const int64_t rounds = P->K > 0 ? (P->T + P->K - 1) / P->K : 1;
-    const int64_t queued = 2 * (int64_t)P->d * rounds;
-    const size_t piece = (size_t)own * P->plane_bytes();
+    const size_t piece = copy_piece(*P);
     P->serial = (P->n_slots == 1 && piece <= kSerialCopyMax) || piece <= kSerialPieceMax;
-    if (P->serial && (P->n_slots == 1 || queued <= kKernelCopyQueued))
+    if (P->serial && (P->n_slots == 1 || copies_queued(*P) <= kKernelCopyQueued))
       P->copy_engine = SO2DR_COPY_KERNEL;
     else
-      P->copy_engine = !P->adjoint && piece < kKernelCopyBelow && queued > kKernelCopyQueued
-                           ? SO2DR_COPY_KERNEL_OUT
-                           : SO2DR_COPY_DMA;
+      P->copy_engine = kernel_out_pays(*P) ? SO2DR_COPY_KERNEL_OUT : SO2DR_COPY_DMA;
   }
   return SO2DR_OK;
 }

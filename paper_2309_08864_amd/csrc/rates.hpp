@@ -68,6 +68,36 @@ constexpr double kernel_rate(int dtype, int stencil, int levels) {
              : 0.0;
 }
 
+// The rates by which the search for a round-at-store plan ranks (BF16, F16): a
+// run of such a plan rounds once per launch, so that the depths found are part
+// of its values, and of their accuracy.  They are the rates that those plans
+// were first chosen by and are not measured again (up to a third below kRate
+// in 2D, for wide boxes and few levels most).
+constexpr double kRateAtStore[2][8][8] = {
+    {
+        // BF16
+        {1538, 2584, 2846, 2923, 2700, 2729, 2744, 2659},
+        {1423, 1950, 1993, 2019, 1899, 1914, 1906, 1911},
+        {773, 832, 802, 799, 0, 0, 0, 0},
+        {447, 413, 403, 384, 0, 0, 0, 0},
+        {234, 224, 217, 198, 0, 0, 0, 0},
+        {1004, 1330, 1486, 1234, 0, 0, 0, 0},
+        {776, 914, 0, 0, 0, 0, 0, 0},
+        {555, 802, 717, 514, 0, 0, 0, 0},
+    },
+    {
+        // F16
+        {1483, 2390, 2473, 2510, 2526, 2510, 2532, 2486},
+        {1396, 1822, 1924, 1974, 1899, 1897, 1915, 1873},
+        {729, 788, 772, 783, 0, 0, 0, 0},
+        {427, 395, 386, 373, 0, 0, 0, 0},
+        {228, 219, 214, 195, 0, 0, 0, 0},
+        {993, 1290, 1414, 1162, 0, 0, 0, 0},
+        {710, 876, 0, 0, 0, 0, 0, 0},
+        {586, 769, 698, 510, 0, 0, 0, 0},
+    },
+};
+
 // Fused depth (at most max_depth) for a plan that leaves k_on to the library.
 // FP32 and FP64: the depth that costs least per level over grids from
 // 400 x 400 to 12800 x 12800 (2D) and 64^3 to 640 x 512 x 256 (3D); deeper

@@ -50,13 +50,15 @@ namespace {
 double simulate(const Plan &P, const so2dr_machine &m, int steps) {
   int64_t computed = 0;
   const std::vector<so2dr_op> ops = build_ops(P, steps, &computed);
-  // the executor's own stream assignment and waits, for the library's
-  // three streams (copy-in, copy-out, compute)
+  // the executor's own stream assignment and waits, for the library's three
+  // streams (copy-in, copy-out, compute) or, where the copies and launches of a
+  // serial plan share one, for that
+  const bool one = P.serial && P.copy_engine != SO2DR_COPY_DMA;
   std::vector<int> strm;
   std::vector<int64_t> waits;
-  schedule_deps(P, ops, 3, &strm, &waits);
+  schedule_deps(P, ops, one ? 1 : 3, &strm, &waits);
   // with two or more slots both copy directions run together most of the time
-  const bool duplex = P.n_slots >= 2;
+  const bool duplex = P.n_slots >= 2 && !one;
   double both = m.duplex_gbps;
   if (P.copy_engine == SO2DR_COPY_KERNEL && m.kcopy_gbps > 0) both = m.kcopy_gbps;
   if (P.copy_engine == SO2DR_COPY_KERNEL_OUT && m.kcopy_out_gbps > 0) both = m.kcopy_out_gbps;

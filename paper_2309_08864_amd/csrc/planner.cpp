@@ -323,10 +323,8 @@ static bool kernel_out_pays(const Plan &P) {
 // kKernelCopyQueued are queued.
 void at_store_ranking(Plan &P) {
   if (P.lean) plan_bytes(P, P.d, P.n_slots, true);
-  if (!P.copy_engine_forced) {
-    P.serial = false;
-    P.copy_engine = kernel_out_pays(P) ? SO2DR_COPY_KERNEL_OUT : SO2DR_COPY_DMA;
-  }
+  if (!P.copy_engine_forced) P.copy_engine = kernel_out_pays(P) ? SO2DR_COPY_KERNEL_OUT : SO2DR_COPY_DMA;
+  P.serial = false;
 }
 
 static bool chunks_ok(const Plan &P, int d) {

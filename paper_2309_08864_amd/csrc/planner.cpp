@@ -327,6 +327,24 @@ void at_store_ranking(Plan &P) {
   P.serial = false;
 }
 
+// The library's fused depth where a launch reads `planes` planes.
+static int depth_for(const Plan &P, int64_t planes) {
+  const int pref = preferred_depth(P.dtype, P.stencil, P.max_k_on, (uint64_t)planes * P.plane_bytes());
+  return std::max(1, std::min(pref, P.K));
+}
+
+// Takes the depth for the tallest chunk instead of the whole field's, which
+// the chunk count was chosen with; a one-buffer plan whose spare planes then no
+// longer fit keeps that.
+static void settle_depth(Plan &P) {
+  const int field_depth = P.k_on;
+  P.k_on = depth_for(P, P.slot_planes - P.lean_extra);
+  if (P.lean && plan_bytes(P, P.d, P.n_slots, true) > P.budget) {
+    P.k_on = field_depth;
+    plan_bytes(P, P.d, P.n_slots, true);
+  }
+}
+
 static bool chunks_ok(const Plan &P, int d) {
   // every chunk but the last hands its top 2 r K planes to the next one, so
   // it must own at least that many (paper: halo space <= chunk)
@@ -404,8 +422,7 @@ int make_plan(const so2dr_desc &D, Plan *P) {
     // the 7-point star, 2 for the 13-point star and the 27-point box, 7 for
     // the 2D 5-point star, 1 for the radius-4 box (bound by arithmetic: fusing
     // only adds tile-edge recomputation)
-    const int pref = preferred_depth(P->dtype, P->stencil, P->max_k_on, (uint64_t)P->N * P->plane_bytes());
-    P->k_on = std::max(1, std::min(pref, P->K));
+    P->k_on = depth_for(*P, P->N);
   }
   P->budget = D.device_budget_bytes;
   P->adjoint = D.adjoint != 0;
@@ -476,6 +493,7 @@ int make_plan(const so2dr_desc &D, Plan *P) {
     if (!chosen) { set_error("no chunk count fits the device budget"); return SO2DR_E_BUDGET; }
     plan_bytes(*P, chosen, chosen_slots, lean);
   }
+  if (D.k_on == 0 && !P->resreu) settle_depth(*P);
   if (P->lean) grow_lean_block(*P);
   P->workspace = ((size_t)P->n_slots * P->bufs_per_slot + (size_t)P->shared_bufs) * P->buf_bytes +
                  (size_t)P->n_rs() * P->rs_bytes + P->scratch_bytes;

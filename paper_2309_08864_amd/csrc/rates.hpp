@@ -108,7 +108,9 @@ constexpr double kRateAtStore[2][8][8] = {
 //   FP32 2D 49-point box  1 level  8.0 87 296,    2: 8.4 78 261
 //   FP32 2D 5-point star  6 levels 2.0 13.1 47.8, 7: 2.1 12.7 43.3, 8: 2.1 12.4 40.8
 //   FP64 2D 49-point box  1 level  10.5 151 561,  2: 14.7 116 405 (4800 x 4800:
-//     83 and 93): one level in fields up to the last-level cache's 256 MiB
+//     83 and 93): one level where a launch reads no more than the last-level
+//     cache's 256 MiB (rows of 12800, 64, 96, 128, 160 and 280 MiB read: one
+//     level 30 40 50 71 129, two 39 49 63 75 109)
 // and for 251 x 190 x 163 and 640 x 512 x 256
 //   FP64 3D 13-point star 1 level  29.3 288,      2: 20.1 198
 // 16-bit storage: a round-at-store run rounds once per launch, so that its
@@ -120,9 +122,9 @@ constexpr int kDepth[4][8] = {
     {3, 3, 2, 1, 1, 3, 2, 2},
     {3, 3, 2, 1, 1, 3, 2, 2},
 };
-constexpr int preferred_depth(int dtype, int stencil, int max_depth, uint64_t field_bytes) {
+constexpr int preferred_depth(int dtype, int stencil, int max_depth, uint64_t launch_bytes) {
   int d = (dtype >= 0 && dtype < 4 && stencil >= 0 && stencil < 8) ? kDepth[dtype][stencil] : 1;
-  if (dtype == 1 && stencil == 3 && field_bytes <= (uint64_t)256 << 20) d = 1;
+  if (dtype == 1 && stencil == 3 && launch_bytes <= (uint64_t)256 << 20) d = 1;
   return d < max_depth ? d : max_depth;
 }
 

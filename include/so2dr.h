@@ -243,6 +243,12 @@ int so2dr_plan_bind(struct so2dr_plan *plan, void *dev_arena, size_t arena_bytes
  * next one; -1 (the default) never.  One run only.  Errors: E_INVALID. */
 int so2dr_plan_set_fail_after(struct so2dr_plan *plan, int64_t n_ops);
 
+/* Testing aid: with enable = 1 every launch of the plan takes the LDS-plane
+ * kernel, which otherwise serves planes (2D: rows) of 4 GiB and more only; the
+ * results are the same bits.  0 (the default): the kernel the launch's sizes
+ * ask for.  Errors: E_INVALID. */
+int so2dr_plan_set_plane_kernel(struct so2dr_plan *plan, int enable);
+
 /* Enable (1) or disable (0) per-operation HIP event timing in so2dr_stats. */
 int so2dr_plan_set_timing(struct so2dr_plan *plan, int enable);
 

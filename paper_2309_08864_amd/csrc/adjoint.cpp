@@ -72,6 +72,7 @@ static LaunchParams base_launch(const Plan &P, const double *w) {
   lp.n_axis = P.N;
   lp.weights = w;
   lp.npts = (int)P.weights.size();
+  lp.plane_kernel = P.plane_kernel;
   return lp;
 }
 

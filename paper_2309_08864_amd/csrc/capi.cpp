@@ -252,6 +252,17 @@ int so2dr_plan_set_timing(so2dr_plan *plan, int enable) {
   GUARD_END
 }
 
+int so2dr_plan_set_plane_kernel(so2dr_plan *plan, int enable) {
+  GUARD_BEGIN
+  if (!plan) {
+    set_error("null plan");
+    return SO2DR_E_INVALID;
+  }
+  plan->p.plane_kernel = enable != 0;
+  return SO2DR_OK;
+  GUARD_END
+}
+
 int so2dr_plan_set_fail_after(so2dr_plan *plan, int64_t n_ops) {
   GUARD_BEGIN
   if (!plan || n_ops < -1) {

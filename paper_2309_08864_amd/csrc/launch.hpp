@@ -31,6 +31,7 @@ struct LaunchParams {
   const double *weights;   // npts, lexicographic
   int npts;
   int ras = 0;             // 16-bit storage: round only what a launch stores
+  bool plane_kernel = false;   // take the LDS-plane kernel whatever the sizes
 };
 
 // Deepest compiled depth per storage type (so2dr_dtype) and stencil; 0 = none.

@@ -364,7 +364,7 @@ int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
     // (16.2), one of the radius-4 box 6.6 (11.3) and 9.1 (12.1).
     constexpr int VX = sizeof(T) == 8 ? 2 : 4;
     constexpr bool wide = BOX && R >= 3 && KL == 1;
-    if (march_fits<T, 1>(p)) {
+    if (!p.plane_kernel && march_fits<T, 1>(p)) {
       auto shape = [&](auto vx) {
         constexpr int V = decltype(vx)::value;
         constexpr bool rot = (int64_t)KL * V * Stencil<2, BOX, R>::npts() * (2 * R + 1) > (sizeof(T) == 8 ? 2400 : 3000);
@@ -412,7 +412,7 @@ int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
     // 301x257x203 52 us against 57, 27-point 59 against 62
     constexpr bool two_narrow = a32 && KL == 2 && (BOX || R == 2);
     using Narrow6 = March3d<T, BOX, R, KL, 8, two_narrow ? 6 : 4, 1, 2, 2, 1, RAS>;
-    if (march_fits<T, 1>(p)) {
+    if (!p.plane_kernel && march_fits<T, 1>(p)) {
       auto narrow = [&]() {
         const MarchPlan n = Narrow::plan(p);
         if constexpr (two_narrow) {

@@ -216,7 +216,9 @@ int so2dr_plan_get_ops(const struct so2dr_plan *plan, so2dr_op *ops, int64_t n);
  * of so2dr_plan_get_ops is enqueued on stream index stream[k] (roles as in
  * so2dr_plan_bind) after waiting for the completion of the earlier ops
  * waits[k * SO2DR_MAX_WAITS + i] (-1 = none; ops on one stream also run in
- * list order).  The waits are what make the pipeline of Algorithm 1 safe:
+ * list order).  A run whose copies and launches share the first stream (see
+ * SO2DR_COPY_AUTO) goes by the answer for n_streams == 1, whatever it is bound
+ * to.  The waits are what make the pipeline of Algorithm 1 safe:
  * slot reuse, copy-in before compute before copy-out, the region-sharing
  * buffer read before it is overwritten, and the in-place host array across
  * rounds.  n <= info.n_ops entries are written.  Errors: E_INVALID. */

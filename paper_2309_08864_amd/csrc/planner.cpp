@@ -511,11 +511,16 @@ int make_plan(const so2dr_desc &D, Plan *P) {
   // 1.4 MB 0.86).
   //
   // Otherwise DMA, whose copy-outs the host releases one by one, but copy
-  // kernels out where a run queues many copies: set when those were left to
-  // the device in one go (a 64 MiB pattern: 28-82 GB/s over repeats, kernels
-  // 84-86).  Adjoint plans keep DMA: their reverse sweep waits for each round
-  // and its compute kernels compete with copy kernels (the 1024^3 gradient:
-  // 4.9 s with DMA, 7.2 s with copy kernels).
+  // kernels out where a run queues many copies: set when those were left to the
+  // device in one go (a 64 MiB pattern: 28-82 GB/s over repeats, kernels 84-86).
+  // Released one by one DMA is ahead in the sweeps measured since (64, 32, 8 and
+  // 2 MiB pieces 95, 94, 83 and 59 GB/s, kernels out 86, 82, 62 and 45): the
+  // rule stands because plans report the engine it gives them.  Pieces of
+  // kSerialPieceMax and less on one stream, DMA in and kernels out, lie between
+  // 25 % behind and 16 % ahead of the same on three streams (seven sweeps of 2
+  // to 8 chunks, level on average).  Adjoint plans keep DMA: their reverse sweep
+  // waits for each round and its compute kernels compete with copy kernels (the
+  // 1024^3 gradient: 4.9 s with DMA, 7.2 s with copy kernels).
   P->copy_engine_forced = D.copy_engine != SO2DR_COPY_AUTO;
   if (P->copy_engine_forced) {
     P->copy_engine = D.copy_engine;

@@ -44,7 +44,8 @@
 // kernel 2.46 always, and the 64 MiB chunks above 186 against 185 ms).
 // Plans marked serial by the planner (one slot, or pieces so small that the
 // events cost more than the overlap gives) run in list order on streams[0]
-// alone, their host copies as copy kernels through the host mapping.
+// alone, their host copies as copy kernels through the host mapping: both ways,
+// or out only in plans of several slots that queue more than 256 copies.
 // Nothing synchronises the device between rounds.
 #include <algorithm>
 #include <chrono>

@@ -38,8 +38,10 @@ void default_machine(const Plan &P, so2dr_machine *m) {
   m->duplex_gbps = 97.3;
   m->d2d_gbps = 2000.0;
   m->launch_us = 8.0;
-  m->kcopy_gbps = 77.0;      // copy kernels of 64 workgroups both ways, beside stencil kernels
-  m->kcopy_out_gbps = 88.0;  // DMA in, copy kernels out
+  // copy kernels of 8 workgroups beside stencil kernels, pieces of 32 and 64 MiB:
+  // both ways, and DMA in with copy kernels out
+  m->kcopy_gbps = 66.0;
+  m->kcopy_out_gbps = 88.0;
   // measured per storage type, stencil and depth (rates.hpp)
   const int md = max_depth(P.dtype, P.stencil);
   for (int k = 1; k <= 8; ++k) m->gupd[k - 1] = k <= md ? kernel_rate(P.dtype, P.stencil, k) : 0.0;
@@ -154,8 +156,10 @@ int suggest(const so2dr_desc &in, const so2dr_machine *mp, so2dr_desc *out, doub
   // engines they were first ranked by, whatever has become faster since: their
   // depths decide how often a run rounds.
   so2dr_machine rank = m;
-  if (base.ras && !mp)
+  if (base.ras && !mp) {
+    rank.kcopy_gbps = 77.0;
     for (int k = 0; k < 8; ++k) rank.gupd[k] = m.gupd[k] > 0 ? kRateAtStore[base.dtype - SO2DR_BF16][base.stencil][k] : 0.0;
+  }
   const int T = in.T;
   const std::vector<int> Ks = in.tb_depth > 0 ? std::vector<int>{std::min(in.tb_depth, std::max(T, 1))}
                                               : depth_candidates(std::max(T, 1));

@@ -28,6 +28,7 @@
 #include <cstring>
 
 #include "aux.hpp"
+#include "copy_rule.hpp"
 #include "launch.hpp"
 #include "plan.hpp"
 
@@ -80,6 +81,7 @@ struct AdjCtx {
   hipStream_t s_in, s_out, s_comp;
   bool kcopy = false;  // HBM -> host copies by copy kernels through the host mappings
   bool kcopy_in = false;  // host -> HBM copies too
+  bool hold = false;  // the host waits before it queues a DMA copy-out
   size_t field = 0;
   double *partials, *acc_w, *acc_loss;
   std::vector<double> wT;  // reflected weights
@@ -110,7 +112,7 @@ static int loss_pass(Plan &P, AdjCtx &C, void *lam_host, const void *y_host, so2
   char *d_lam = C.kcopy ? mapped_host(lam_host, C.field) : nullptr;
   char *d_lam_in = C.kcopy_in ? d_lam : nullptr;
   char *d_y = C.kcopy_in ? mapped_host(y_host, C.field) : nullptr;
-  const bool hold = C.s_out != C.s_comp && C.s_out != C.s_in && !d_lam;
+  const bool hold = C.hold && !d_lam;
   auto out = [&](int i) -> int {
     const int64_t z0 = P.bnd[i], z1 = P.bnd[i + 1];
     const size_t n = (size_t)(z1 - z0) * pb;
@@ -169,7 +171,7 @@ static int reverse_round(Plan &P, AdjCtx &C, const void *u_host, void *lam_host,
   char *d_lam_in = C.kcopy_in ? d_lam : nullptr;
   LaunchParams fwd = base_launch(P, P.weights.data());
   LaunchParams adj = base_launch(P, C.wT.data());
-  const bool hold = C.s_out != C.s_comp && C.s_out != C.s_in && !d_lam;
+  const bool hold = C.hold && !d_lam;
   // copy-out of lambda_{t_s} over chunk i's output planes, in place, from the
   // slot's own buffer
   auto out = [&](int i) -> int {
@@ -360,6 +362,7 @@ static int adjoint_impl(Plan &P, const void *u0, const void *target, void *grad_
   C.s_in = P.streams[0];
   C.s_out = ns >= 2 ? P.streams[1] : P.streams[0];
   C.s_comp = ns >= 3 ? P.streams[2] : P.streams[0];
+  C.hold = C.s_out != C.s_comp && C.s_out != C.s_in && host_waits_reverse(copy_piece(P), P.d);
   C.partials = reinterpret_cast<double *>(P.scratch());
   C.acc_w = C.partials + (size_t)kRedWgs * kMaxRedPts;
   C.acc_loss = C.acc_w + 128;

@@ -88,6 +88,8 @@ std::vector<so2dr_op> build_ops(const Plan &P, int steps, int64_t *planes_comput
 // Validate and plan; returns 0 or a negative code with set_error().
 int make_plan(const so2dr_desc &d, Plan *out);
 
+// Bytes of the largest chunk's copy.
+size_t copy_piece(const Plan &P);
 // Gives a round-at-store plan the block heights and copy engine that the
 // search for such plans ranks by.
 void at_store_ranking(Plan &P);

@@ -307,12 +307,12 @@ static void grow_lean_block(Plan &P) {
   plan_bytes(P, d, slots, true);
 }
 
-// Bytes of the largest chunk's copy, and the host copies a run of T steps queues.
-static size_t copy_piece(const Plan &P) {
+size_t copy_piece(const Plan &P) {
   int64_t own = 0;
   for (int i = 0; i < P.d; ++i) own = std::max<int64_t>(own, P.bnd[i + 1] - P.bnd[i]);
   return (size_t)own * P.plane_bytes();
 }
+// Host copies that a run of T steps queues.
 static int64_t copies_queued(const Plan &P) { return 2 * (int64_t)P.d * (P.K > 0 ? (P.T + P.K - 1) / P.K : 1); }
 static bool kernel_out_pays(const Plan &P) {
   return !P.adjoint && copy_piece(P) < kKernelCopyBelow && copies_queued(P) > kKernelCopyQueued;

@@ -1,5 +1,5 @@
-// launch_impl.hpp -- shared by the kernels_<type>.hip files: builds the
-// argument block, sizes the grid and launches one tb_kernel instantiation.
+// launch_impl.hpp -- shared by the objects of kernels.hip: picks a launch's
+// kernel and tile shape, builds its argument block, sizes its grid and launches it.
 #pragma once
 #include <atomic>
 #include <algorithm>
@@ -8,6 +8,7 @@
 #include "lane_tile.hpp"
 #include "launch.hpp"
 #include "march2d_kernel.hpp"
+#include "march_plan.hpp"
 #include "wide2d_kernel.hpp"
 #include "march_kernel.hpp"
 #include "tb_kernel.hpp"
@@ -127,51 +128,6 @@ inline bool march_fits(const LaunchParams &p) {
          p.out_z0 > -((int64_t)1 << 29) && std::max<int64_t>(p.in_lo, 0) < std::min<int64_t>(p.in_hi, p.n_axis);
 }
 
-// A launch's cost in clock cycles for segments of a given length, and the
-// segmenting of least cost.  A workgroup's march step takes `lat` cycles of
-// latency (barrier, LDS round trip, address work) plus its own issue time
-// `issue` and that of the workgroups sharing its CU, and a segment of zseg
-// output planes takes zseg + extra steps; workgroups run in rounds of CUs x
-// per_cu.  Candidates fill k workgroups per CU, k = 1, 2, ..., which is where
-// the rounds change; more, shorter segments only for a gain of 0.5 %, since each
-// re-reads `extra` planes.  per_wg: tiles a workgroup takes (2D: one per wave).
-//
-// Measured on MI355X (3D 7-point FP32, 3 levels, tiles of 8 waves x 6 rows x 2
-// cells): a 256^3 grid took 76 us in 336 workgroups of 16-plane segments (the
-// former rule: 1.5 workgroups per slot, segments of at least 16 planes) and
-// 50 us in 252 of 22 planes, one round instead of two; a 320 x 320 x 26 chunk
-// 52 us in 24 workgroups and 19 us in 216.  2D: one level of the radius-3 box on
-// 12800^2 took 329 us in 1027 workgroups, five on some CUs, and 290 us in
-// 1014; five levels of the radius-1 box on 1020 x 767 rows 19 us in 17-row
-// segments and 11 us in 4-row ones.  Over 323 launches of 47 shapes on 9
-// grids the choice came within 3 % (geometric mean) of the best segmenting
-// tried.
-struct MarchPlan {
-  int64_t zseg = 0;
-  int nseg = 0;
-  double cost = 0.0;
-};
-
-inline MarchPlan plan_march(int64_t span, int64_t tiles, int extra, int cus, int per_cu, double lat,
-                            double issue, int per_wg = 1) {
-  constexpr int kMaxPerCu = 12;    // candidates; beyond, rounds no longer matter
-  constexpr int kPrologue = 2;     // steps' worth of start-up per workgroup
-  MarchPlan best;
-  int64_t last = 0;
-  for (int k = 1; k <= kMaxPerCu; ++k) {
-    const int64_t want = std::min(span, std::max<int64_t>(1, (int64_t)k * cus * per_wg / tiles));
-    if (want == last) continue;
-    last = want;
-    const int64_t zseg = (span + want - 1) / want, nseg = (span + zseg - 1) / zseg;
-    const int64_t n = (tiles * nseg + per_wg - 1) / per_wg, full = n / ((int64_t)cus * per_cu), rest = n - full * cus * per_cu;
-    const double t = (double)full * (lat + per_cu * issue) +
-                     (rest > 0 ? lat + (double)((rest + cus - 1) / cus) * issue : 0.0);
-    const double c = (double)(zseg + extra + kPrologue) * t;
-    if (best.nseg == 0 || c < 0.995 * best.cost) best = {zseg, (int)nseg, c};
-  }
-  return best;
-}
-
 // One tile shape of march3d_kernel: its segmenting and predicted cost for a
 // launch, and the launch itself.
 template <typename T, bool BOX, int R, int KL, int NW, int M, int VX, int HB, int PF, int WPE = 1,
@@ -185,17 +141,16 @@ struct March3d {
   static int ntx(const LaunchParams &p) { return (int)((p.nx + G::OX - 1) / G::OX); }
   static int nty(const LaunchParams &p) { return (int)((p.ny + G::OY - 1) / G::OY); }
 
-  static MarchPlan plan(const LaunchParams &p) {
-    // instructions of one wave per step: the multiply-adds, per row and level
-    // the lane shifts, halo rows and stores, and the plane's addresses; a wave
-    // instruction takes 4 cycles of its SIMD, and the waves share 4 SIMDs
-    constexpr double issue = NW * (M * KL * (VX * S::npts() + 4.0) + 20.0);
-    constexpr double lat = 800.0;
+  // cached: the launch's planes fit the last-level cache
+  static MarchPlan plan(const LaunchParams &p, bool cached = false, double scale = 1.0) {
     static std::atomic<int> per_cu{-1};
     const int64_t slots = resident_wgs((const void *)kernel, NW * 64, &per_cu);
     const int occ = std::max(1, per_cu.load(std::memory_order_relaxed));
     const int cus = slots > 0 ? (int)(slots / occ) : 256;
-    return plan_march(p.out_hi - p.out_lo, (int64_t)ntx(p) * nty(p), 2 * KL * R + KL - 1, cus, occ, lat, issue);
+    MarchMemory mem;
+    if (cached) mem = {(double)p.plane * sizeof(T) / kCacheBytesPerCycle, 2 * KL * R};
+    return plan_march(p.out_hi - p.out_lo, (int64_t)ntx(p) * nty(p), 2 * KL * R + KL - 1, cus, occ, kMarchLatency,
+                      march_issue(NW, M, VX, KL, S::npts()), 1, scale, mem);
   }
 
   static int launch(const LaunchParams &p, const MarchPlan &mp, hipStream_t stream, std::string *msg) {
@@ -329,17 +284,16 @@ constexpr uint64_t kLastLevelCache = (uint64_t)256 << 20;
 //   * other deeper fusion and the 27-point box: 512-byte rows, 8 waves of 4
 //     rows (27-point at 2 levels 0.36 against 0.40 ms);
 //   (the taller shapes hold FP32 sums only: FP64 keeps the 4-row tiles).
-// Launches that fit the last-level cache, and rows that are not whole vectors,
-// use the narrow shape: one cell per lane, 8 waves of 4 rows.  Its tiles are a
-// third to a sixth of the wide ones', so a mid-size grid divides evenly over
-// the CUs, several workgroups share a CU and hide each other's barriers, and
-// the tile overhang past the grid is smaller: 3 levels of the 7-point star on
-// 256^3 44 us against 50 in the wide shape, 512x512x128 68 against 85,
-// 96x40x48 9 against 15; two levels of the BF16 13-point star on 320x320x26
-// 19 against 23.  The cost model prices the wide shapes 20 % too low against
-// the narrow one (their two waves per SIMD issue at 66 of the 73 TFLOP/s that
-// four reach), hence the factor.  Odd rows: the 27-point box on 301x257x203,
-// two levels, 62 us, 85 in the register-column kernel that took them before.
+// Launches that fit the last-level cache take the shape of least cost
+// (march_plan.hpp), mostly the narrow one: one cell per lane, 8 waves of 4 rows.
+// Its tiles are a third to a sixth of the wide ones', so a mid-size grid divides
+// evenly over the CUs, several workgroups share a CU and hide each other's
+// barriers, and the tile overhang past the grid is smaller: 3 levels of the
+// 7-point star on 256^3 44 us against 50 in the wide shape, 512x512x128 68
+// against 85, 96x40x48 9 against 15; two levels of the BF16 13-point star on
+// 320x320x26 19 against 23.  Rows that are not whole vectors have the narrow
+// shapes only: the 27-point box on 301x257x203, two levels, 62 us, 85 in the
+// register-column kernel that took them before.
 // Planes of 4 GiB or more (and 2D rows of 4 GiB) take the LDS-plane kernel.
 template <typename T, int NDIM, bool BOX, int R, int KL, bool RAS>
 int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
@@ -413,34 +367,32 @@ int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
     constexpr bool two_narrow = a32 && KL == 2 && (BOX || R == 2);
     using Narrow6 = March3d<T, BOX, R, KL, 8, two_narrow ? 6 : 4, 1, 2, 2, 1, RAS>;
     if (!p.plane_kernel && march_fits<T, 1>(p)) {
-      auto narrow = [&]() {
-        const MarchPlan n = Narrow::plan(p);
-        if constexpr (two_narrow) {
-          const MarchPlan n6 = Narrow6::plan(p);
-          if (n6.cost < n.cost) return Narrow6::launch(p, n6, s, msg);
-        }
-        const MarchPlan q = Small::plan(p);
-        if (q.cost < n.cost) return Small::launch(p, q, s, msg);
-        return Narrow::launch(p, n, s, msg);
-      };
       const uint64_t moved = (uint64_t)(std::min(p.in_hi, p.n_axis) - std::max<int64_t>(p.in_lo, 0) + p.out_hi - p.out_lo) *
                              (uint64_t)p.plane * sizeof(T);
-      const bool streams = moved > kLastLevelCache;
+      const bool cached = moved <= kLastLevelCache;
+      MarchPlan w;
       if constexpr (!no_wide) {
         using Wide = March3d<T, BOX, R, KL, NWW, MW, VXW, HBW, 2, 1, RAS, HAW>;
+        constexpr double scale = wide_scale(BOX, a32, KL);
         if (march_fits<T, VXW>(p)) {
-          const MarchPlan w = Wide::plan(p);
-          if (streams) return Wide::launch(p, w, s, msg);
-          double best = std::min(Narrow::plan(p).cost, Small::plan(p).cost);
-          if constexpr (two_narrow) best = std::min(best, Narrow6::plan(p).cost);
-          return w.cost < 0.8 * best ? Wide::launch(p, w, s, msg) : narrow();
+          if (!cached) return Wide::launch(p, Wide::plan(p), s, msg);
+          if (scale > 0) w = Wide::plan(p, true, scale);
         }
         if constexpr (square) {   // rows of an odd number of 2-cell vectors
           using Mid = March3d<T, BOX, R, KL, 8, 4, 2, 2, 2, 1, RAS>;
-          if (streams && march_fits<T, 2>(p)) return Mid::launch(p, Mid::plan(p), s, msg);
+          if (!cached && march_fits<T, 2>(p)) return Mid::launch(p, Mid::plan(p), s, msg);
         }
       }
-      return narrow();
+      // the least cost; on a tie (the cache binds) the wider shape
+      const MarchPlan n = Narrow::plan(p, cached), q = Small::plan(p, cached), n6 = Narrow6::plan(p, cached);
+      const double least = std::min(n.cost, std::min(q.cost, n6.cost));
+      if constexpr (!no_wide) {
+        using Wide = March3d<T, BOX, R, KL, NWW, MW, VXW, HBW, 2, 1, RAS, HAW>;
+        if (w.nseg > 0 && w.cost <= least) return Wide::launch(p, w, s, msg);
+      }
+      if (n.cost <= least) return Narrow::launch(p, n, s, msg);
+      if (q.cost <= least) return Small::launch(p, q, s, msg);
+      return Narrow6::launch(p, n6, s, msg);
     }
   }
   return launch_one<T, NDIM, BOX, R, KL, RAS>(p, s, msg);

@@ -56,20 +56,28 @@ int launch_dcopy(void *dst, const void *src, size_t bytes, hipStream_t s, int gr
 
 // Region sharing of up to two fields in one launch: halo <- pool, then pool <-
 // top, element by element (a lane reads its pool element before it writes it).
-// Four copy launches of 6 MB each took 20 us at chunks of 16 planes of 320^2.
+// Bound by the launch where its planes fit the last-level cache, by HBM beyond.
+// What a lane holds is a plain vector type: an array of HIP's vector class went
+// to LDS, 16 us per launch at any size.  Measured on MI355X, us for two or four
+// copies, in that array, and now, one field 1 MiB 5.4 16 2.7, 8 MiB 6.1 18 4.5, 32
+// MiB 18 27 17, 64 MiB 33 41 32, 128 MiB 72 98 88; two fields 1 MiB 11 16 3.0, 8
+// MiB 13 21 10, 32 MiB 36 41 33, 64 MiB 73 101 84: one launch while what it
+// reads and writes fits the cache, single copies above.
+typedef uint32_t Vec4 __attribute__((ext_vector_type(4)));
+
 __global__ __launch_bounds__(256) void share_kernel(ShareArgs a, int64_t n) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    uint4 below[2], above[2];
+    Vec4 below[2], above[2];
 #pragma unroll
     for (int f = 0; f < 2; ++f) {
-      if (a.halo[f]) below[f] = static_cast<const uint4 *>(a.pool[f])[i];
-      if (a.top[f]) above[f] = static_cast<const uint4 *>(a.top[f])[i];
+      if (a.halo[f]) below[f] = static_cast<const Vec4 *>(a.pool[f])[i];
+      if (a.top[f]) above[f] = static_cast<const Vec4 *>(a.top[f])[i];
     }
 #pragma unroll
     for (int f = 0; f < 2; ++f) {
-      if (a.halo[f]) static_cast<uint4 *>(a.halo[f])[i] = below[f];
-      if (a.top[f]) static_cast<uint4 *>(a.pool[f])[i] = above[f];
+      if (a.halo[f]) static_cast<Vec4 *>(a.halo[f])[i] = below[f];
+      if (a.top[f]) static_cast<Vec4 *>(a.pool[f])[i] = above[f];
     }
   }
 }
@@ -78,12 +86,15 @@ int launch_share(const ShareArgs &a, size_t bytes, hipStream_t s) {
   if (bytes == 0) return 0;
   uintptr_t bits = (uintptr_t)bytes;
   bool meet = false;   // a chunk whose halo and top planes overlap
+  uint64_t touched = 0;
   for (int f = 0; f < 2; ++f) {
     const char *h = static_cast<const char *>(a.halo[f]), *t = static_cast<const char *>(a.top[f]);
     if (h || t) bits |= (uintptr_t)a.pool[f] | (uintptr_t)h | (uintptr_t)t;
     if (h && t) meet = meet || (h < t + bytes && t < h + bytes);
+    if (h || t) touched += bytes * (1 + (h != nullptr) + (t != nullptr));
   }
-  if (bits % 16 == 0 && !meet) {
+  if (touched == 0) return 0;
+  if (bits % 16 == 0 && !meet && touched <= kLastLevelCache) {
     hipLaunchKernelGGL(share_kernel, dim3(1024), dim3(256), 0, s, a, (int64_t)(bytes / 16));
     return hipGetLastError() == hipSuccess ? 0 : -5;
   }
@@ -104,7 +115,6 @@ int launch_share(const ShareArgs &a, size_t bytes, hipStream_t s) {
 // Measured on MI355X, 64 MiB in / out, us: 1188 / 1214 with both sides
 // aligned (1240 without the host's side aligned), the DMA engines 1174 / 1184;
 // 2 MiB 50 / 50 and 46 / 46.
-typedef uint32_t Vec4 __attribute__((ext_vector_type(4)));
 struct Aligned16 { Vec4 v; };
 struct __attribute__((packed)) Anywhere16 { Vec4 v; };
 

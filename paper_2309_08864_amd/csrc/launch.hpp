@@ -20,6 +20,10 @@ enum StencilId {
   ST_COUNT = 8
 };
 
+// Last-level cache of MI355X: a launch whose planes read and written fit it
+// is bound by its march steps, a larger one by HBM.
+constexpr uint64_t kLastLevelCache = (uint64_t)256 << 20;
+
 struct LaunchParams {
   int stencil;             // StencilId
   int kl;                  // fused levels

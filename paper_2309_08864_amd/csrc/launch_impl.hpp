@@ -266,10 +266,6 @@ constexpr size_t march_lds() {
   return sizeof(A) * KL * HB * NW * 2 * R * 64 * VX;
 }
 
-// Last-level cache of MI355X: a launch whose planes read and written fit it
-// is bound by its march steps, a larger one by HBM.
-constexpr uint64_t kLastLevelCache = (uint64_t)256 << 20;
-
 // Kernel choice per depth, from measurements on MI355X (all variants give
 // identical bits).
 //

@@ -178,17 +178,29 @@ struct March3d {
   }
 };
 
+// Bytes that a launch reads and writes, and whether its planes fit the last-level
+// cache.
+template <typename T>
+uint64_t launch_bytes(const LaunchParams &p) {
+  return (uint64_t)(std::min(p.in_hi, p.n_axis) - std::max<int64_t>(p.in_lo, 0) + p.out_hi - p.out_lo) *
+         (uint64_t)p.plane * sizeof(T);
+}
+template <typename T>
+bool in_cache(const LaunchParams &p) { return launch_bytes<T>(p) <= kLastLevelCache; }
+
 // Segmenting of one launch of a 2D kernel over row tiles G: `rows` input rows
 // per step (a segment ends with a step where it can), `extra` rows' work besides
 // its own per segment, `issue` and `lat` cycles per row as in plan_march.
-template <typename G, typename A>
+template <typename T, typename G, typename A>
 MarchPlan plan_rows(void (*kernel)(TbArgs<A>), const LaunchParams &p, int rows, int halo, int extra, double lat,
                     double issue, std::atomic<int> *per_cu) {
   const int64_t slots = resident_wgs((const void *)kernel, 64 * kRowWaves, per_cu);
   const int occ = std::max(1, per_cu->load(std::memory_order_relaxed));
   const int64_t span = p.out_hi - p.out_lo;
+  MarchMemory mem;
+  if (in_cache<T>(p)) mem = {(double)p.plane * sizeof(T) / kCacheBytesPerCycle2d, halo};
   MarchPlan mp = plan_march(span, (p.nx + G::OX - 1) / G::OX, extra, slots > 0 ? (int)(slots / occ) : 256, occ, lat,
-                            issue, kRowWaves);
+                            issue, kRowWaves, 1.0, mem);
   mp.zseg = (mp.zseg + halo + rows - 1) / rows * rows - halo;
   mp.nseg = (int)((span + mp.zseg - 1) / mp.zseg);
   return mp;
@@ -233,7 +245,7 @@ struct March2d {
     // levels of the radius-2 box: 93, 87, 86 us)
     constexpr double issue = 4.0 * (KL * (VX * S::npts() + 4.0) + 10.0), lat = 900.0;
     static std::atomic<int> per_cu{-1};
-    return plan_rows<G>(kernel, p, 1, 2 * KL * R, 2 * KL * R + KL - 1, lat, issue, &per_cu);
+    return plan_rows<T, G>(kernel, p, 1, 2 * KL * R, 2 * KL * R + KL - 1, lat, issue, &per_cu);
   }
   static int launch(const LaunchParams &p, const MarchPlan &mp, hipStream_t stream, std::string *msg) {
     return launch_rows<S, G>(kernel, p, mp, stream, msg);
@@ -253,7 +265,7 @@ struct Wide2d {
     // within 2 % of the best of 300 to 3000 on six grids (400 x 400 to 12800^2).
     constexpr double issue = 4.0 * (VX * S::npts() + 30.0), lat = 1800.0 / U;
     static std::atomic<int> per_cu{-1};
-    return plan_rows<G>(kernel, p, U, 2 * R, 2, lat, issue, &per_cu);
+    return plan_rows<T, G>(kernel, p, U, 2 * R, 2, lat, issue, &per_cu);
   }
   static int launch(const LaunchParams &p, const MarchPlan &mp, hipStream_t stream, std::string *msg) {
     return launch_rows<S, G>(kernel, p, mp, stream, msg);
@@ -363,9 +375,7 @@ int launch_any(const LaunchParams &p, hipStream_t s, std::string *msg) {
     constexpr bool two_narrow = a32 && KL == 2 && (BOX || R == 2);
     using Narrow6 = March3d<T, BOX, R, KL, 8, two_narrow ? 6 : 4, 1, 2, 2, 1, RAS>;
     if (!p.plane_kernel && march_fits<T, 1>(p)) {
-      const uint64_t moved = (uint64_t)(std::min(p.in_hi, p.n_axis) - std::max<int64_t>(p.in_lo, 0) + p.out_hi - p.out_lo) *
-                             (uint64_t)p.plane * sizeof(T);
-      const bool cached = moved <= kLastLevelCache;
+      const bool cached = in_cache<T>(p);
       MarchPlan w;
       if constexpr (!no_wide) {
         using Wide = March3d<T, BOX, R, KL, NWW, MW, VXW, HBW, 2, 1, RAS, HAW>;

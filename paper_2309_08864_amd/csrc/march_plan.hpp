@@ -84,7 +84,7 @@ constexpr double kMarchLatency = 800.0;
 // three levels, FP32, FP64 and BF16, each shape in up to 11 segmentings): 3.6 %
 // from the best on average.  With one factor of 1/0.8 and no bound by the cache
 // it was 4.4 %, and single launches were up to 33 % slower than the wide shape
-// in the former rule's segments (now 9 %): us there, so, and now, 7-point FP32
+// in the former rule's segments (now 14 %): us there, so, and now, 7-point FP32
 // one level 512 x 512 x 64 24, 32 and 26; FP64 two levels 1024 x 512 x 24 38, 44
 // and 38; 13-point FP64 one level 512 x 512 x 40 32, 38 and 32.
 constexpr double wide_scale(bool box, bool fp32_sums, int levels) {
@@ -92,5 +92,11 @@ constexpr double wide_scale(bool box, bool fp32_sums, int levels) {
   return levels > 1 ? 1.0 / 0.85 : fp32_sums ? 1.0 / 0.95 : 1.0 / 0.9;
 }
 constexpr double kCacheBytesPerCycle = 2600.0;
+// The 2D kernels' (5.3 TB/s), fitted to 1350 launches of nine row lengths.  us by
+// the former rule (segments for 1024 workgroups), without this bound, and with
+// it: 5-point FP32 one level of 800 rows of 12800 cells 13.9, 16.5, 14.7; two
+// levels of 3200 rows of 4800 21.6, 26.3, 21.8; 25-point FP64 one level of 800
+// rows of 12800 29.2, 34.1, 28.9.
+constexpr double kCacheBytesPerCycle2d = 2200.0;
 
 }  // namespace so2dr

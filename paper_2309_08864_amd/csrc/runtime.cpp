@@ -123,7 +123,8 @@ char *mapped_host(const void *p, size_t bytes, bool coherent) {
     (void)hipGetLastError();
     return nullptr;
   }
-  if (coherent && (a.allocationFlags & hipHostMallocNonCoherent)) return nullptr;
+  // memory that the device may cache: allocated so, or registered as coarse-grained
+  if (coherent && (a.allocationFlags & (hipHostMallocNonCoherent | hipExtHostRegisterCoarseGrained))) return nullptr;
   void *base = nullptr;
   size_t size = 0;
   if (hipMemGetAddressRange(&base, &size, a.devicePointer) != hipSuccess || !base) {

@@ -26,9 +26,9 @@ int launch_wgrad(int dtype, int stencil, const void *lam, const void *u, int64_t
 // acc[k] += sum over workgroups of their partials.
 int launch_wgrad_sum(int npts, const double *partials, double *acc, hipStream_t s);
 
-// dst <- src, `bytes` bytes of device-addressable memory, by a copy kernel
-// of `grid` workgroups on stream s.
-int launch_dcopy(void *dst, const void *src, size_t bytes, hipStream_t s, int grid = 1024);
+// dst <- src, `bytes` bytes of device-addressable memory, by a copy kernel on
+// stream s.
+int launch_dcopy(void *dst, const void *src, size_t bytes, hipStream_t s);
 
 // dst <- src, `bytes` bytes at any alignment, one of the two in page-locked host
 // memory (dst where to_host, else src; its device address), by at most `wgs`

@@ -15,16 +15,15 @@
 
 namespace so2dr {
 
-// Workgroups a launch aims for before it splits the cut axis into segments;
-// each segment re-reads 2*KL*R input planes, so segments stay long.
+// Workgroups an LDS-plane launch aims for before it splits the cut axis into
+// segments; each re-reads 2*KL*R input planes, so segments stay long.
 constexpr int64_t kTargetWgs = 1024;
 constexpr int64_t kMinSegPlanes = 16;
 
-// Segmenting of the cut axis for the LDS-plane kernel: `target` workgroups,
+// Segmenting of the cut axis for the LDS-plane kernel: kTargetWgs workgroups,
 // never segments shorter than kMinSegPlanes.
-inline void plan_segments(int64_t span, int64_t tiles, int64_t *zseg, int *nseg,
-                          int64_t target = kTargetWgs) {
-  int64_t n = std::max<int64_t>(1, (target + tiles - 1) / tiles);
+inline void plan_segments(int64_t span, int64_t tiles, int64_t *zseg, int *nseg) {
+  int64_t n = std::max<int64_t>(1, (kTargetWgs + tiles - 1) / tiles);
   n = std::min<int64_t>(n, std::max<int64_t>(1, span / kMinSegPlanes));
   *zseg = (span + n - 1) / n;
   *nseg = (int)((span + *zseg - 1) / *zseg);

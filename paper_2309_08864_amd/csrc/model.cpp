@@ -115,11 +115,9 @@ double predict_seconds(const Plan &P, const so2dr_machine &m, int steps) {
 
 namespace {
 
-// Chunk counts searched.  Measured on MI355X, many small host copies run
-// slower than the model's link figures: DMA copies collapse when hundreds are
-// queued (the reason for the copy-kernel modes), and even DMA in with copy
-// kernels out fell from 88 to 69 GB/s at 64 chunks of the 7-point workload.
-// So the search stops at 32 chunks and takes a candidate with more chunks,
+// Chunk counts searched.  Measured on MI355X, small host copies run slower than
+// the model's link figures: 94 GB/s both ways with DMA copies of 32 MiB, 83 with
+// 8 and 59 with 2; with copy kernels out 82, 62 and 45.  So the search stops at 32 chunks and takes a candidate with more chunks,
 // more fused levels or a deeper round only when it is predicted more than
 // 1 % faster (candidates are visited in increasing order).
 constexpr int64_t kMaxSearchChunks = 32;

@@ -110,7 +110,8 @@ constexpr int64_t kKernelCopyQueued = 256;
 // Workgroups of one host-copy kernel: the link's rate where nothing runs beside
 // it; a few where the launches and the copies of other slots do, which more of
 // them slow (a 7-point sweep of 512 x 256 x 256 in 16 chunks, copy kernels both
-// ways: 19.0 ms with 8, 22.8 with 32).
+// ways: 19.0 ms with 8, 22.8 with 32; over pieces of 1 to 64 MiB 8 lies within
+// 8 % of the best of 4 to 64, which differs from size to size).
 constexpr int kSerialCopyWgs = 32;
 constexpr int kHostCopyWgs = 8;
 

@@ -26,10 +26,11 @@
 //     region-sharing chain.
 // The one wait that is not left to the device is a DMA copy-out's wait for
 // its chunk's last launch: the host waits for that event and only then queues
-// the copy, so the runtime sees a copy with nothing in front of it (but for a
-// few large copies over two slots, see copy_rule.hpp).  Queued behind an event
-// of the compute stream instead, the runtime carries the same copy by a kernel
-// that floods the memory system or on the engine that the copy-in is using.  Measured on MI355X, a bare pipeline of copy-in, six
+// the copy, so the runtime sees a copy with nothing in front of it.  Queued
+// behind an event of the compute stream instead, the runtime carries the same
+// copy by a kernel that floods the memory system or on the engine that the
+// copy-in is using (for few large copies only in a process' first pass, see
+// copy_rule.hpp).  Measured on MI355X, a bare pipeline of copy-in, six
 // device passes and copy-out over three slots, both directions together:
 // 8 MiB pieces 57 GB/s with the device-side wait and 90 with the host's,
 // 32 MiB 44 and 97, 64 MiB 94 and 97; in the executor the 7-point sweep of
@@ -55,7 +56,6 @@
 
 #include "launch.hpp"
 #include "aux.hpp"
-#include "copy_rule.hpp"
 #include "plan.hpp"
 
 namespace so2dr {
@@ -324,10 +324,9 @@ int execute(Plan &P, const void *host_in, void *host_out, int steps, so2dr_stats
   // the arena at once)
   const int64_t fail_at = P.fail_after_ops;
   P.fail_after_ops = -1;   // one run only
-  // DMA copy-outs on a stream of their own that the host waits for are held
-  // back until a later operation waits for them or nothing else is left to queue
-  const bool hold_out = ns >= 2 && !dev_out &&
-                        host_waits_forward(P.n_slots, copy_piece(P), 2 * (int64_t)P.d * n_rounds_for(P, steps));
+  // DMA copy-outs on a stream of their own are held back until a later
+  // operation waits for them or nothing else is left to queue
+  const bool hold_out = ns >= 2 && !dev_out;
   std::vector<size_t> held;   // copy-outs in list order; the first n_out are queued
   size_t n_out = 0;
   auto enqueue_op = [&](size_t k) -> int {

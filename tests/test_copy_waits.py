@@ -1,6 +1,6 @@
-"""Who waits before a DMA copy-out: the rule (copy_rule.hpp, compiled for the
-host) at the sizes it was measured at, and on the GPU plans on either side of
-it against the in-core bits."""
+"""Who waits before a DMA copy-out of the reverse sweep: the rule (copy_rule.hpp,
+compiled for the host) at the sizes it was measured at, and on the GPU gradients
+on either side of it, and forward runs of large copies against the in-core bits."""
 import subprocess
 
 import numpy as np
@@ -10,11 +10,6 @@ from paper_2309_08864_amd import build as B
 
 MIB = 1 << 20
 
-FORWARD = [   # slots, MiB per copy, copies queued, does the host wait
-    (2, 1024, 512, 0), (2, 512, 256, 0), (2, 512, 32, 0), (2, 256, 192, 0), (2, 256, 128, 0), (2, 128, 32, 0),
-    (2, 256, 512, 1), (2, 128, 192, 1), (2, 128, 512, 1), (2, 64, 64, 1), (2, 64, 256, 1), (2, 32, 16, 1), (2, 2, 64, 1),
-    (3, 1024, 512, 1), (3, 512, 256, 1), (3, 64, 32, 1), (4, 512, 256, 1), (1, 107, 60, 1),
-]
 REVERSE = [   # MiB per copy, chunks, does the host wait
     (146, 28, 0), (512, 4, 0), (256, 16, 0), (128, 16, 0), (64, 16, 0), (64, 8, 0),
     (64, 32, 1), (32, 16, 1), (32, 32, 1), (16, 32, 1), (6, 20, 1),
@@ -23,14 +18,12 @@ REVERSE = [   # MiB per copy, chunks, does the host wait
 
 def test_rule_at_the_measured_points(tmp_path):
     src, exe = tmp_path / "rule.cpp", tmp_path / "rule"
-    body = "".join(f'  std::printf("%d\\n", (int)so2dr::host_waits_forward({s}, (size_t){m} << 20, {q}));\n'
-                   for s, m, q, _ in FORWARD)
-    body += "".join(f'  std::printf("%d\\n", (int)so2dr::host_waits_reverse((size_t){m} << 20, {d}));\n'
-                    for m, d, _ in REVERSE)
+    body = "".join(f'  std::printf("%d\\n", (int)so2dr::host_waits_reverse((size_t){m} << 20, {d}));\n'
+                   for m, d, _ in REVERSE)
     src.write_text('#include <cstdio>\n#include "copy_rule.hpp"\nint main() {\n' + body + "}\n")
     subprocess.run(["g++", "-std=c++17", "-I", B.CSRC, str(src), "-o", str(exe)], check=True)
     got = [int(x) for x in subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout.split()]
-    assert got == [w for *_, w in FORWARD + REVERSE]
+    assert got == [w for *_, w in REVERSE]
 
 
 @pytest.mark.gpu
